@@ -172,12 +172,14 @@ struct KBlockArgs {
     double *carry;
     // batched FP64 with the monitor: U of sigma group g at U + g * u_gstride
     int64_t u_gstride = 0;
-    // CSR only: the dense-head panel (kblock_csr_panel_bytes(n) bytes, prepared
-    // once with launch_csr_panel_init); null keeps the broadcast kernels
+    // CSR only: memory of the sampled rows' dense panel (csr_panel_bytes of it,
+    // at least csr_panel_min_bytes(n); prepared once with
+    // launch_csr_panel_init); null keeps the broadcast kernel
     void *csr_panel = nullptr;
+    size_t csr_panel_bytes = 0;
     // CSR: the longest row of A (stored entries) when the caller knows it, else
-    // -1; a chunk of sampled rows that cannot exceed the dense-head panel then
-    // skips the broadcast launch that would only run for an overflowing chunk
+    // -1; a chunk of sampled rows that cannot exceed the panel then skips the
+    // broadcast launch that would only run for an overflowing chunk
     int64_t csr_max_row = -1;
     // dense single-problem FP64 product: tile configuration, resolved once by
     // the caller together with the row-group count the finish pass sums
@@ -238,7 +240,10 @@ void f64_config_shape(int id, int *bm, int *bn, int *waves);
 int f64_config_id(int64_t n, int32_t sb);
 int tune_lookup(int32_t compute, int64_t n, int32_t sb);   // -1: no entry
 void tune_store(int32_t compute, int64_t n, int32_t sb, int id);   // id < 0 removes
-size_t kblock_csr_panel_bytes(int64_t n);
+// Panel memory of the CSR product: what every workspace holds, and what a
+// workspace allocated by the call holds (room for wide chunks of long rows).
+size_t csr_panel_min_bytes(int64_t n);
+size_t csr_panel_full_bytes(const kdcd_matrix *A);
 hipError_t launch_csr_panel_init(const kdcd_matrix *A, void *panel, hipStream_t st);
 int64_t kblock_mixed_row_groups(int cfg, int64_t m, int64_t n, int32_t sb, int32_t compute,
                                 bool batch);

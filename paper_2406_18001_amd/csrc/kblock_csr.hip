@@ -23,9 +23,11 @@
 // entry each; the entries' (value, mask, offset) are then broadcast to the
 // row's lanes in storage order, and lane jl accumulates a * B[c][jl] whenever
 // its bit is set.  Every sum runs in a fixed order: results are deterministic.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
+#include "csr_panel.hpp"
 
 namespace kdcd {
 namespace {
@@ -35,7 +37,6 @@ constexpr int CSR_VMAX = 3072;        // stored entries of one chunk of sampled 
 static_assert(CSR_VMAX <= 32767, "value offsets are 16-bit");
 constexpr int CSR_HS = 4096;          // hash slots (power of two, > CSR_VMAX)
 constexpr int CSR_MAXGROUPS = 512;    // row groups of the U-part
-constexpr double kCsrWaveMinAvg = 128.0;   // average row length from which rows get a wave each
 
 __device__ __forceinline__ int64_t clampi(int64_t v, int64_t lo, int64_t hi)
 {
@@ -436,155 +437,6 @@ __global__ __launch_bounds__(CSR_NT) __attribute__((amdgpu_waves_per_eu(RPW > 1 
                 double s = 0.0;
                 for (int w = 0; w < NW * RPW; ++w) s += red(w, tid);
                 partial[(int64_t)blockIdx.x * sb + j0 + tid] = s;
-            }
-        }
-        __syncthreads();
-        j0 = j1;
-    }
-}
-
-// Long rows (chunks of at most WJ = 8 sampled rows): one wave walks one data
-// row, 64 stored entries at a time (coalesced loads), each lane keeping its
-// own partial sums for the chunk's sampled rows; the lanes' sums meet in a
-// fixed xor tree at the end of the row, so the result is deterministic.
-constexpr int WJ = 8;
-
-template <int KIND>
-__global__ __launch_bounds__(CSR_NT) __attribute__((amdgpu_waves_per_eu(4))) void kblock_csr_wave_kernel(
-    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx,
-    const double *__restrict__ val, int64_t m, int64_t nnz, const int32_t *__restrict__ S,
-    int32_t sb, const double *__restrict__ norms, KParams kp, const double *__restrict__ beta,
-    const double *__restrict__ bscale, double *__restrict__ partial, double *__restrict__ W,
-    int32_t n_row_groups, double *__restrict__ carry, int32_t *status, int32_t jbeg,
-    int32_t jend, const int32_t *__restrict__ gate, double *__restrict__ U)
-{
-    constexpr int NW = CSR_NT / 64;
-    constexpr int NB = KIND == KDCD_KERNEL_RBF ? 2 : 4;   // entries per lane per batch
-    using MaskT = uint32_t;
-    __shared__ int32_t hkey[CSR_HS];
-    __shared__ MaskT hmask[CSR_HS];
-    __shared__ int16_t hbase[CSR_HS];      // value offsets (< CSR_VMAX)
-    __shared__ uint32_t hfilt[CSR_FBITS / 32];
-    __shared__ double hval[CSR_VMAX];
-    __shared__ int32_t rowoff[WJ + 1];
-    __shared__ int32_t scan[CSR_NT];
-    __shared__ double red[NW][WJ];
-
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const bool is_w = (int)blockIdx.x >= n_row_groups;
-    if (is_w && W == nullptr) return;
-    const int wblk = (int)blockIdx.x - n_row_groups;   // W-part: sampled rows [wblk*NW, +NW)
-    auto rp = [&](int64_t r) { return clampi(row_ptr[clampi(r, 0, m)], 0, nnz); };
-
-    if (gate && *gate == 0) return;
-    for (int j0 = jbeg; j0 < jend;) {
-        int j1 = build_panel<MaskT, WJ>(j0, -1, row_ptr, col_idx, val, m, nnz, S, jend, hkey, hfilt,
-                                        hmask, hbase, hval, rowoff, scan, status);
-        int npieces = 1;
-        if (j1 == -2) {                  // a sampled row longer than the panel: in pieces
-            if (!carry) {
-                if (tid == 0) set_status(status, KDCD_ERR_UNSUPPORTED);
-                return;
-            }
-            const int64_t r = clampi(S[j0], 0, m - 1);
-            npieces = (int)((rp(r + 1) - rp(r) + CSR_VMAX - 1) / CSR_VMAX);
-            j1 = j0 + 1;
-        }
-        const int nj = j1 - j0;
-        // lane j < nj owns sampled row j0 + j for the map and the reduction
-        const bool jok = lane < nj;
-        const int64_t Sj = clampi(S[j0 + (jok ? lane : 0)], 0, m - 1);
-        const double nbj = (KIND == KDCD_KERNEL_RBF) ? norms[Sj] : 0.0;
-        double colsum = 0.0;
-        for (int pc = 0; pc < npieces; ++pc) {
-        if (npieces > 1) {               // dot products summed over the pieces in carry[]
-            __syncthreads();
-            build_panel<MaskT, WJ>(j0, pc, row_ptr, col_idx, val, m, nnz, S, jend, hkey, hfilt, hmask,
-                                   hbase, hval, rowoff, scan, status);
-        }
-        const bool last = pc + 1 == npieces;
-        const int64_t r_first = is_w ? (int64_t)wblk * NW + wid : (int64_t)blockIdx.x * NW + wid;
-        const int64_t r_end = is_w ? min((int64_t)sb, (int64_t)(wblk + 1) * NW) : m;
-        const int64_t r_step = is_w ? NW : (int64_t)n_row_groups * NW;
-        for (int64_t rix = r_first; rix < r_end; rix += r_step) {
-            const int64_t row = is_w ? clampi(S[rix], 0, m - 1) : rix;
-            const int64_t e_beg = rp(row), len = rp(row + 1) - e_beg;
-            double acc[WJ];
-#pragma unroll
-            for (int j = 0; j < WJ; ++j) acc[j] = 0.0;
-            int32_t cb[NB], nc[NB];
-            double vb[NB], nv[NB];
-            auto load_batch = [&](int64_t eb, int32_t (&c)[NB], double (&v)[NB]) {
-#pragma unroll
-                for (int u = 0; u < NB; ++u) {
-                    const int64_t off = eb + (int64_t)u * 64 + lane;
-                    const int64_t ec = clampi(e_beg + off, 0, nnz - 1);
-                    const bool ok = off < len;
-                    c[u] = ok ? col_idx[ec] : -1;
-                    v[u] = ok ? val[ec] : 0.0;
-                }
-            };
-            constexpr int64_t STEP = (int64_t)NB * 64;
-            if (len > 0) load_batch(0, cb, vb);
-            for (int64_t eb = 0; eb < len; eb += STEP) {
-                if (eb + STEP < len) load_batch(eb + STEP, nc, nv);
-#pragma unroll
-                for (int u = 0; u < NB; ++u) {
-                    if (cb[u] >= 0) {
-                        const int h = hash_find(hkey, hfilt, cb[u]);
-                        if (h >= 0) {
-                            const MaskT msk = hmask[h];
-                            const int bs = hbase[h];
-                            const double a = vb[u];
-#pragma unroll
-                            for (int j = 0; j < WJ; ++j)
-                                if ((msk >> j) & 1u)
-                                    acc[j] += a * hval[bs + popc((MaskT)(msk & ((1u << j) - 1u)))];
-                        }
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < NB; ++u) {
-                    cb[u] = nc[u];
-                    vb[u] = nv[u];
-                }
-            }
-            double mine = 0.0;
-#pragma unroll
-            for (int j = 0; j < WJ; ++j) {
-                double v = acc[j];
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-                if (lane == j) mine = v;
-            }
-            if (jok) {
-                if (npieces > 1) {
-                    const int64_t ci = is_w ? m + rix : row;
-                    if (pc > 0) mine += carry[ci];
-                    if (!last) carry[ci] = mine;
-                }
-                if (last) {
-                    const double na = (KIND == KDCD_KERNEL_RBF) ? norms[row] : 0.0;
-                    const double kv = kernel_map<KIND>(mine, na, nbj, row == Sj, kp);
-                    if (is_w) {
-                        W[rix * sb + j0 + lane] = kv;
-                    } else {
-                        double bv = beta[row];
-                        if (bscale) bv *= bscale[row];
-                        colsum += bv * kv;
-                        if (U) U[(int64_t)(j0 + lane) * m + row] = kv;
-                    }
-                }
-            }
-        }
-        }   // pieces
-        if (!is_w) {
-            if (lane < WJ) red[wid][lane] = colsum;
-            __syncthreads();
-            if (tid < nj) {
-                double t = 0.0;
-                for (int w = 0; w < NW; ++w) t += red[w][tid];
-                partial[(int64_t)blockIdx.x * sb + j0 + tid] = t;
             }
         }
         __syncthreads();
@@ -1089,9 +941,9 @@ int64_t groups_for(int64_t m)
 
 }  // namespace
 
-// Lanes per row (LPR = 64 / RPW): no more than the sampled rows need, and
-// few enough that a chunk of LPR average-length sampled rows fits the panel
-// (long rows: narrow chunks, several data rows per wave).
+// Lanes per row (LPR = 64 / RPW) of the broadcast kernel: no more than the
+// sampled rows need, and few enough that a chunk of LPR average-length sampled
+// rows fits the panel (long rows: narrow chunks, several data rows per wave).
 int csr_rows_per_wave(const kdcd_matrix *A, int32_t sb)
 {
     int lpr = sb <= 8 ? 8 : (sb <= 16 ? 16 : (sb <= 32 ? 32 : 64));
@@ -1100,36 +952,46 @@ int csr_rows_per_wave(const kdcd_matrix *A, int32_t sb)
     return 64 / lpr;
 }
 
-// Kernel choice: long rows (average >= kCsrWaveMinAvg at <= 8 sampled rows per
-// chunk) -> one wave per row; more than 16 sampled rows -> the dense-head
-// kernel; otherwise the broadcast / scatter kernel.
-enum CsrPath { CSR_BROADCAST, CSR_WAVE, CSR_HEAD };
-CsrPath csr_path(const kdcd_matrix *A, int32_t sb)
+// Kernel choice by the average row length (a property of A alone, so that one
+// panel memory serves every launch of a solve): long rows -> the dense-panel
+// product; short rows -> the dense-head kernel (more than 16 sampled rows) or
+// the broadcast / scatter kernel.
+enum CsrPath { CSR_BROADCAST, CSR_PANEL, CSR_HEAD };
+CsrPath csr_path(const KBlockArgs &a)
 {
-    const int rpw = csr_rows_per_wave(A, sb);
-    if (rpw == 8 && (double)A->nnz >= kCsrWaveMinAvg * (double)A->m) return CSR_WAVE;
-    return sb > 16 ? CSR_HEAD : CSR_BROADCAST;
+    const kdcd_matrix *A = a.A;
+    if (csr_long_rows(A) && csr_panel_plan(a).lpr) return CSR_PANEL;
+    return a.sb > 16 && a.csr_panel && !csr_long_rows(A) ? CSR_HEAD : CSR_BROADCAST;
 }
 
-int64_t kblock_csr_row_groups(const kdcd_matrix *A, int32_t sb)
+int64_t kblock_csr_row_groups(const KBlockArgs &a)
 {
-    if (csr_path(A, sb) == CSR_HEAD) {
-        const int64_t steps = (A->m + HD_RB - 1) / HD_RB;   // 16 rows per step
-        return steps < HD_MAXGROUPS ? steps : HD_MAXGROUPS;
+    const kdcd_matrix *A = a.A;
+    switch (csr_path(a)) {
+    case CSR_PANEL: return csr_panel_groups(A);
+    case CSR_HEAD: return std::min<int64_t>((A->m + HD_RB - 1) / HD_RB, HD_MAXGROUPS);   // 16 rows per step
+    default: return groups_for(A->m);
     }
-    return groups_for(A->m);
 }
 
-int64_t kblock_csr_max_row_groups(int64_t m)
+int64_t kblock_csr_max_row_groups(const kdcd_matrix *A)
 {
-    const int64_t head = std::min<int64_t>((m + HD_RB - 1) / HD_RB, HD_MAXGROUPS);
-    return std::max<int64_t>(head, groups_for(m));
+    // (the panel product takes at most one row group per 16 rows, at most 1024)
+    const int64_t head = std::min<int64_t>((A->m + HD_RB - 1) / HD_RB, HD_MAXGROUPS);
+    return std::max<int64_t>(head, groups_for(A->m));
 }
 
-size_t kblock_csr_panel_bytes(int64_t n) { return panel_bytes(n); }
+size_t csr_panel_min_bytes(int64_t n) { return std::max(panel_bytes(n), csr_dense_panel_min_bytes(n)); }
+
+size_t csr_panel_full_bytes(const kdcd_matrix *A)
+{
+    return csr_long_rows(A) ? std::max(csr_panel_min_bytes(A->n), csr_dense_panel_full_bytes(A))
+                            : csr_panel_min_bytes(A->n);
+}
 
 hipError_t launch_csr_panel_init(const kdcd_matrix *A, void *panel, hipStream_t st)
 {
+    if (csr_long_rows(A)) return launch_csr_dense_panel_init(A, panel, st);
     const int64_t blocks = std::min<int64_t>((A->n + 255) / 256, 4096);
     hipLaunchKernelGGL(csr_panel_init_kernel, dim3((unsigned)std::max<int64_t>(blocks, 1)), dim3(256),
                        0, st, panel, A->n);
@@ -1140,12 +1002,12 @@ hipError_t launch_kblock_csr(const KBlockArgs &a, hipStream_t st)
 {
     const kdcd_matrix *A = a.A;
     const int rpw = csr_rows_per_wave(A, a.sb);
-    const CsrPath path = csr_path(A, a.sb);
-    if (path == CSR_HEAD && a.csr_panel) {
+    const CsrPath path = csr_path(a);
+    if (path == CSR_HEAD) {
         // per chunk of HD_NJ sampled rows: panel build, dense-head pass, and the
         // broadcast kernel gated on the build's fallback flag (left out when the
         // longest row of A says that the chunk fits the panel)
-        const int64_t groups = kblock_csr_row_groups(A, a.sb);
+        const int64_t groups = kblock_csr_row_groups(a);
         const int64_t n_w = a.W ? (a.sb + HD_RB - 1) / HD_RB : 0;
         const PanelPtrs q = panel_ptrs(a.csr_panel, A->n);
         const int64_t rows_per_wg_b = (CSR_NT / 64) * rpw;
@@ -1198,54 +1060,52 @@ hipError_t launch_kblock_csr(const KBlockArgs &a, hipStream_t st)
         }
         return hipGetLastError();
     }
-    // long rows: one wave per data row and per-lane sums (chunks of <= 8 rows)
-    const bool wave = path == CSR_WAVE;
-    const int64_t groups = kblock_csr_row_groups(A, a.sb);
-    const int rows_per_wg = (CSR_NT / 64) * (wave ? 1 : rpw);
+    const int64_t rows_per_wg = (CSR_NT / 64) * rpw;
     const int64_t n_w = a.W ? (a.sb + rows_per_wg - 1) / rows_per_wg : 0;
-    dim3 grid((unsigned)(groups + n_w)), block(CSR_NT);
+    // the broadcast kernel on sampled rows [jbeg, jend)
+    auto broadcast = [&](int64_t groups, int32_t jbeg, int32_t jend, const int32_t *gate) {
+        dim3 grid((unsigned)(groups + n_w)), block(CSR_NT);
 #define KDCD_CSR(RPW, KIND)                                                                   \
     KDCD_TIMED_LAUNCH((kblock_csr_kernel<RPW, KIND>), grid, block, 0, st, A->row_ptr,          \
                        A->col_idx, A->values, A->m, A->nnz, a.S, a.sb, a.norms, a.kp, a.beta,  \
-                       a.beta_scale, a.partial, a.W, (int32_t)groups, a.carry, a.status, 0, a.sb, \
-                       nullptr, a.U)
+                       a.beta_scale, a.partial, a.W, (int32_t)groups, a.carry, a.status, jbeg, \
+                       jend, gate, a.U)
 #define KDCD_CSR_KIND(RPW)                                                                    \
     switch (a.kp.kind) {                                                                      \
     case KDCD_KERNEL_LINEAR: KDCD_CSR(RPW, KDCD_KERNEL_LINEAR); break;                        \
     case KDCD_KERNEL_POLY: KDCD_CSR(RPW, KDCD_KERNEL_POLY); break;                            \
     default: KDCD_CSR(RPW, KDCD_KERNEL_RBF); break;                                           \
     }
-    if (wave) {
-        switch (a.kp.kind) {
-        case KDCD_KERNEL_LINEAR:
-            KDCD_TIMED_LAUNCH((kblock_csr_wave_kernel<KDCD_KERNEL_LINEAR>), grid, block, 0, st,
-                               A->row_ptr, A->col_idx, A->values, A->m, A->nnz, a.S, a.sb, a.norms,
-                               a.kp, a.beta, a.beta_scale, a.partial, a.W, (int32_t)groups, a.carry, a.status,
-                               0, a.sb, nullptr, a.U);
-            break;
-        case KDCD_KERNEL_POLY:
-            KDCD_TIMED_LAUNCH((kblock_csr_wave_kernel<KDCD_KERNEL_POLY>), grid, block, 0, st,
-                               A->row_ptr, A->col_idx, A->values, A->m, A->nnz, a.S, a.sb, a.norms,
-                               a.kp, a.beta, a.beta_scale, a.partial, a.W, (int32_t)groups, a.carry, a.status,
-                               0, a.sb, nullptr, a.U);
-            break;
-        default:
-            KDCD_TIMED_LAUNCH((kblock_csr_wave_kernel<KDCD_KERNEL_RBF>), grid, block, 0, st,
-                               A->row_ptr, A->col_idx, A->values, A->m, A->nnz, a.S, a.sb, a.norms,
-                               a.kp, a.beta, a.beta_scale, a.partial, a.W, (int32_t)groups, a.carry, a.status,
-                               0, a.sb, nullptr, a.U);
-            break;
+        switch (rpw) {
+        case 1: KDCD_CSR_KIND(1) break;
+        case 2: KDCD_CSR_KIND(2) break;
+        case 4: KDCD_CSR_KIND(4) break;
+        default: KDCD_CSR_KIND(8) break;
         }
-        return hipGetLastError();
-    }
-    switch (rpw) {
-    case 1: KDCD_CSR_KIND(1) break;
-    case 2: KDCD_CSR_KIND(2) break;
-    case 4: KDCD_CSR_KIND(4) break;
-    default: KDCD_CSR_KIND(8) break;
-    }
 #undef KDCD_CSR_KIND
 #undef KDCD_CSR
+    };
+    if (path == CSR_BROADCAST) {
+        broadcast(groups_for(A->m), 0, a.sb, nullptr);
+        return hipGetLastError();
+    }
+    // per chunk: the panel product, and the broadcast kernel gated on the
+    // panel's overflow flag where the chunk's columns may not fit.  A timed
+    // launch covers the first chunk's product (one chunk), or the span from it
+    // to the last chunk's.
+    const CsrPanelPlan plan = csr_panel_plan(a);
+    const int32_t groups_b = csr_panel_fallback_groups(A);
+    const ArmedEvents armed = armed_events();
+    const bool one = a.sb <= plan.lpr;
+    if (!one) armed_events() = ArmedEvents{nullptr, nullptr};
+    for (int32_t j0 = 0; j0 < a.sb; j0 += plan.lpr) {
+        const int32_t nj = std::min<int32_t>(plan.lpr, a.sb - j0);
+        if (!one && j0 == 0 && armed.start) (void)hipEventRecord(armed.start, st);
+        const hipError_t e = launch_csr_panel_chunk(a, plan, j0, nj, one, st);
+        if (e != hipSuccess) return e;
+        if (!one && j0 + nj == a.sb && armed.stop) (void)hipEventRecord(armed.stop, st);
+        if (!plan.sure) broadcast(groups_b, j0, j0 + nj, csr_panel_gate(a.csr_panel));
+    }
     return hipGetLastError();
 }
 

@@ -20,8 +20,8 @@ using namespace kdcd;
 namespace kdcd {
 hipError_t launch_kblock_mixed(const KBlockArgs &a, hipStream_t st);
 hipError_t launch_kblock_csr(const KBlockArgs &a, hipStream_t st);
-int64_t kblock_csr_row_groups(const kdcd_matrix *A, int32_t sb);
-int64_t kblock_csr_max_row_groups(int64_t m);
+int64_t kblock_csr_row_groups(const KBlockArgs &a);
+int64_t kblock_csr_max_row_groups(const kdcd_matrix *A);
 hipError_t launch_convert_lowp(const kdcd_matrix *A, int32_t compute, void *hi, void *lo,
                                int64_t ldlow, float *normlow, hipStream_t st);
 int krr_recur_threads(int32_t b, int32_t sk);
@@ -51,7 +51,7 @@ constexpr int64_t kMaxGroups = 1024;   // upper bound on row groups of any kerne
 // kernel-block launch on A.
 int64_t max_row_groups(const kdcd_matrix *A)
 {
-    if (A->format == KDCD_CSR) return kblock_csr_max_row_groups(A->m);
+    if (A->format == KDCD_CSR) return kblock_csr_max_row_groups(A);
     return std::min<int64_t>(kMaxGroups, (A->m + 63) / 64);   // dense tiles are >= 64 rows
 }
 // From this block width on, the Gram rows come from the U-part (two small
@@ -113,7 +113,7 @@ int64_t bind_config(KBlockArgs &kb, bool batch = false)
 {
     const kdcd_matrix *A = kb.A;
     kb.cfg = -1;
-    if (A->format == KDCD_CSR) return kblock_csr_row_groups(A, kb.sb);
+    if (A->format == KDCD_CSR) return kblock_csr_row_groups(kb);
     if (kb.compute == KDCD_F64) {
         kb.cfg = batch ? f64_batch_config_id(A->n, kb.sb) : f64_config_id(A->n, kb.sb);
         return kblock_f64_row_groups(kb.cfg, A->m, A->n, kb.sb, batch);
@@ -147,6 +147,7 @@ size_t lowp_elem_bytes(int32_t compute) { return compute == KDCD_F32 ? 4 : 2; }
 // Workspace regions of one solve.
 struct Layout {
     size_t status, norms, partial, r, W, Dinv, iota, hi, lo, normlow, pos, carry, panel, total;
+    size_t panel_bytes;   // CSR: size of the sampled rows' panel region
     // K-RR lookahead (la_ok): second row table and Gram, the kernel rows of the
     // previous block's coordinates, its summed updates and their coordinates
     bool la_ok;
@@ -159,6 +160,16 @@ struct Layout {
     // second stored kernel block for the lookahead loop with the monitor (0: none)
     size_t mon_U2;
 };
+
+// A workspace that the call allocates itself holds the full CSR panel, a
+// caller's (kdcd_workspace_bytes) the smallest one.
+void grow_panel(Layout &L, const kdcd_matrix *A, const kdcd_options *opt)
+{
+    if (A->format != KDCD_CSR || (opt && opt->workspace)) return;
+    L.panel = L.total;
+    L.panel_bytes = csr_panel_full_bytes(A);
+    L.total += align256(L.panel_bytes);
+}
 
 void add_monitor(Layout &L, int64_t m, int64_t sbmax)
 {
@@ -202,7 +213,8 @@ Layout make_layout(int32_t problem, const kdcd_matrix *A, const kdcd_kernel *ker
     L.carry = off;   // CSR: partial dot products of sampled rows longer than the panel
     off += (A->format == KDCD_CSR) ? align256(sizeof(double) * (size_t)(A->m + sb)) : 0;
     L.panel = off;   // CSR: the dense-head panel of a chunk of sampled rows
-    off += (A->format == KDCD_CSR) ? align256(kblock_csr_panel_bytes(A->n)) : 0;
+    L.panel_bytes = (A->format == KDCD_CSR) ? csr_panel_min_bytes(A->n) : 0;
+    off += align256(L.panel_bytes);
     L.ldlow = 0;
     L.hi = L.lo = L.normlow = off;
     if (compute != KDCD_F64) {
@@ -965,6 +977,7 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
     if (A->format == KDCD_CSR) {
         base.carry = ws.at<double>(L.carry);
         base.csr_panel = ws.at<void>(L.panel);
+        base.csr_panel_bytes = L.panel_bytes;
         base.csr_max_row = sa.csr_max_row;
         if (R.setup) KDCD_HIP_TRY(launch_csr_panel_init(A, base.csr_panel, st));
     }
@@ -1411,6 +1424,7 @@ kdcd_status run_solve(const SolveArgs &sa)
     kdcd_status rc = check_monitor(sa.A, sa.opt);
     if (rc != KDCD_OK) return rc;
     Layout L = make_layout(sa.problem, sa.A, sa.kernel, sa.b, sa.s, sa.opt.compute);
+    grow_panel(L, sa.A, &sa.opt);
     if (sa.opt.monitor_every > 0) {
         add_monitor(L, sa.A->m, (int64_t)sa.s * sa.b);
         // the lookahead loop keeps two stored kernel blocks (not in a caller's
@@ -2208,7 +2222,8 @@ kdcd_status kdcd_kernel_rhs(const kdcd_matrix *A, const kdcd_kernel *kernel, con
     if (!S || !beta || !r || sb < 1) return KDCD_ERR_INVALID_ARG;
     if (sb > kMaxSB) return KDCD_ERR_UNSUPPORTED;
     const hipStream_t st = (hipStream_t)stream;
-    const Layout L = make_layout(0, A, kernel, 1, sb, compute);
+    Layout L = make_layout(0, A, kernel, 1, sb, compute);
+    grow_panel(L, A, nullptr);
     Workspace ws;
     if ((rc = acquire(ws, L, nullptr, st)) != KDCD_OK) return rc;
     int32_t *status = ws.at<int32_t>(L.status);
@@ -2237,6 +2252,7 @@ kdcd_status kdcd_kernel_rhs(const kdcd_matrix *A, const kdcd_kernel *kernel, con
     if (A->format == KDCD_CSR) {
         base.carry = ws.at<double>(L.carry);
         base.csr_panel = ws.at<void>(L.panel);
+        base.csr_panel_bytes = L.panel_bytes;
         KDCD_HIP_TRY(launch_csr_panel_init(A, base.csr_panel, st));
     }
     KBlockArgs kb;
@@ -2260,7 +2276,8 @@ static kdcd_status kernel_matvec(const kdcd_matrix *A, const kdcd_kernel *kernel
 {
     const int64_t m = A->m;
     const int32_t chunk = kMaxSB;
-    const Layout L = make_layout(2, A, kernel, 1, chunk, KDCD_F64);
+    Layout L = make_layout(2, A, kernel, 1, chunk, KDCD_F64);
+    grow_panel(L, A, nullptr);
     Workspace ws;
     kdcd_status rc = acquire(ws, L, nullptr, st);
     if (rc != KDCD_OK) return rc;
@@ -2290,6 +2307,7 @@ static kdcd_status kernel_matvec(const kdcd_matrix *A, const kdcd_kernel *kernel
         if (A->format == KDCD_CSR) {
             a.carry = ws.at<double>(L.carry);
             a.csr_panel = ws.at<void>(L.panel);
+            a.csr_panel_bytes = L.panel_bytes;
             if (c0 == 0) KDCD_HIP_TRY(launch_csr_panel_init(A, a.csr_panel, st));
         }
         const int64_t groups = bind_config(a);
