@@ -157,6 +157,7 @@ struct KBlockArgs {
     int32_t compute;
     int32_t w_only;          // FP64 kernel: compute the Gram tiles only (no U-part)
     const BatchDesc *batch;  // non-null: batched epilogue (dense F64 and mixed kernels)
+    int32_t batch_nprob;     // its problems (batched; sizes the FP64 launch's LDS)
     double *U;               // dense F64 only: non-null stores K(a_p, a_{S_j}) at U[j*m + p]
     const int32_t *stop;     // dense F64 only: non-null and set -> the launch does nothing
     // dense F64 only: when non-null, W is taken from the U-part rows of the
@@ -237,7 +238,7 @@ int64_t kblock_f64_row_groups(int cfg, int64_t m, int64_t n, int32_t sb, bool ba
 // Tile configurations of the FP64 product and the process-wide tuning table.
 int f64_config_count();
 void f64_config_shape(int id, int *bm, int *bn, int *waves);
-int f64_config_id(int64_t n, int32_t sb);
+int f64_config_id(int64_t m, int64_t n, int32_t sb);   // m < 0: any large m
 int tune_lookup(int32_t compute, int64_t n, int32_t sb);   // -1: no entry
 void tune_store(int32_t compute, int64_t n, int32_t sb, int id);   // id < 0 removes
 // Panel memory of the CSR product: what every workspace holds, and what a
@@ -250,7 +251,7 @@ int64_t kblock_mixed_row_groups(int cfg, int64_t m, int64_t n, int32_t sb, int32
 // Tile configurations of the batched products, tuned under compute + KDCD_TUNE_BATCH.
 int f64_batch_config_count();
 void f64_batch_config_shape(int id, int *bm, int *bn, int *waves);
-int f64_batch_config_id(int64_t n, int32_t sb);
+int f64_batch_config_id(int64_t m, int64_t n, int32_t sb, int32_t nprob);   // m < 0: any large m
 int mixed_batch_config_count();
 void mixed_batch_config_shape(int id, int *bm, int *bn, int *waves);
 int mixed_batch_config_id(int32_t compute, int64_t n, int32_t sb);

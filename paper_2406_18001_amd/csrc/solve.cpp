@@ -58,12 +58,11 @@ int64_t max_row_groups(const kdcd_matrix *A)
 // launches per outer iteration) instead of tiles of their own, which at
 // these widths add a round of workgroups.
 constexpr int64_t kGatherMinSB = 256;
-// Tile configuration of the FP64 Gram-only launches that follow a
-// low-precision product: 128 x 16 (four waves) spreads an s*b-row Gram over
-// the most workgroups; with its long K loop and few tiles that launch is bound
-// by latency, not by the tile's MFMA rate (C2's 1024 x 512 lookahead Gram:
-// 29.8 us against 34.3 for the 64 x 64 tile, 40.3 for 128 x 32).
-constexpr int32_t kGramCfg = 0;
+// Tile configurations (single problem, batched) of the FP64 Gram-only launches
+// that follow a low-precision product: 64 x 16 spreads an s*b-row Gram over the
+// most workgroups; with its long K loop and few tiles that launch is bound by
+// latency, not by the tile's MFMA rate.
+constexpr int32_t kGramCfg = 6, kGramBatchCfg = 0;
 // Largest rank of a low-rank factor (Nystrom landmarks, columns of Phi).
 constexpr int64_t kMaxRank = 4096;
 
@@ -115,7 +114,8 @@ int64_t bind_config(KBlockArgs &kb, bool batch = false)
     kb.cfg = -1;
     if (A->format == KDCD_CSR) return kblock_csr_row_groups(kb);
     if (kb.compute == KDCD_F64) {
-        kb.cfg = batch ? f64_batch_config_id(A->n, kb.sb) : f64_config_id(A->n, kb.sb);
+        kb.cfg = batch ? f64_batch_config_id(A->m, A->n, kb.sb, kb.batch_nprob)
+                       : f64_config_id(A->m, A->n, kb.sb);
         return kblock_f64_row_groups(kb.cfg, A->m, A->n, kb.sb, batch);
     }
     if (!batch && kb.compute != KDCD_F32) {
@@ -137,7 +137,7 @@ hipError_t launch_kblock(const KBlockArgs &a, hipStream_t st)
     KBlockArgs w = a;
     w.compute = KDCD_F64;
     w.w_only = 1;
-    w.cfg = kGramCfg;    // (a.cfg names a low-precision tile)
+    w.cfg = a.batch ? kGramBatchCfg : kGramCfg;    // (a.cfg names a low-precision tile)
     w.U = nullptr;       // the stored kernel block is the low-precision product's
     return launch_kblock_f64(w, st);
 }
@@ -1649,6 +1649,7 @@ kdcd_status kdcd_batch_solve(const kdcd_matrix *A, const kdcd_kernel *kernel, in
     base.status = status;
     base.compute = o.compute;
     base.batch = dbd;
+    base.batch_nprob = n_problems;
     KBlockArgs kb;
     if ((rc = prepare_lowp(base, L, ws, st, kb)) != KDCD_OK) return rc;
 
@@ -2168,6 +2169,7 @@ kdcd_status kdcd_autotune_batch(const kdcd_matrix *A, const kdcd_kernel *kernel,
     kb.status = ws.at<int32_t>(L.status);
     kb.compute = compute;
     kb.batch = ws.at<BatchDesc>(o_bd);
+    kb.batch_nprob = n_problems;
     KBlockArgs low;
     if ((rc = prepare_lowp(kb, L, ws, st, low)) != KDCD_OK) return rc;
     kb = low;
@@ -2433,6 +2435,7 @@ kdcd_status kdcd_batch_eval(const kdcd_matrix *A, const kdcd_kernel *kernel,
         a.status = status;
         a.compute = KDCD_F64;
         a.batch = dbd;
+        a.batch_nprob = n_problems;
         const int64_t groups = bind_config(a, true);
         KDCD_HIP_TRY(launch_kblock(a, st));
         FinishDesc fd{};

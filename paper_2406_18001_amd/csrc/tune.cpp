@@ -101,8 +101,8 @@ kdcd_status kdcd_tune_set(int32_t compute, int64_t n, int32_t sb, int32_t id)
 int32_t kdcd_tune_get(int32_t compute, int64_t n, int32_t sb)
 {
     if (config_count(compute) == 0 || n < 1 || sb < 1 || sb > kMaxSB) return -1;
-    if (compute == KDCD_F64) return f64_config_id(n, sb);
-    if (compute == KDCD_F64 + KDCD_TUNE_BATCH) return f64_batch_config_id(n, sb);
+    if (compute == KDCD_F64) return f64_config_id(-1, n, sb);
+    if (compute == KDCD_F64 + KDCD_TUNE_BATCH) return f64_batch_config_id(-1, n, sb, 1);
     if (compute >= KDCD_TUNE_BATCH) return mixed_batch_config_id(compute - KDCD_TUNE_BATCH, n, sb);
     return lowp_config_id(compute, n, sb);
 }
