@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "svm_persist.hpp"
 #include "sampler.hpp"
 
 using namespace kdcd;
@@ -1419,6 +1420,73 @@ kdcd_status run_graph_windowed(const SolveArgs &sa, const Layout &L)
     return read_status(reinterpret_cast<int32_t *>(e->ws + L.status), sa.st);
 }
 
+// Workgroups of the one-launch K-SVM solve (svm_persist.hip), or 0 when the solve
+// takes its ordinary launches: it needs memory of the call's own, writes nothing
+// but alpha and trace, and repeats the sums of a product on 64-row tiles with one
+// tile per row group, which is what small problems get.
+int64_t persist_groups(const SolveArgs &sa)
+{
+    const kdcd_options &o = sa.opt;
+    if (sa.problem != 0 || sa.A->format != KDCD_DENSE || o.compute != KDCD_F64 || o.workspace ||
+        o.monitor_every > 0 || o.snapshot_every > 0 || o.profile || (o.flags & KDCD_FLAG_GRAPH))
+        return 0;
+    const int64_t groups = svm_persist_groups(sa.A, sa.kernel->kind, sa.s, (sa.H + sa.s - 1) / sa.s);
+    if (groups == 0) return 0;
+    for (const int64_t sb : {(int64_t)sa.s, sa.H % sa.s}) {
+        if (sb == 0) continue;
+        const int id = f64_config_id(sa.A->m, sa.A->n, (int32_t)sb);
+        int bm, bn, w;
+        f64_config_shape(id, &bm, &bn, &w);
+        if (bm != 64 || kblock_f64_row_groups(id, sa.A->m, sa.A->n, (int32_t)sb) != groups) return 0;
+    }
+    return groups;
+}
+
+// The one-launch solve in the workspace at `base`; *done says whether alpha is final
+// (otherwise it is as it was, and the ordinary launches take over).
+kdcd_status run_persist(const SolveArgs &sa, const Layout &L, char *base, size_t o_save, size_t o_slots,
+                        int64_t groups, bool *done)
+{
+    const kdcd_matrix *A = sa.A;
+    int32_t *status = reinterpret_cast<int32_t *>(base + L.status);
+    double *norms = reinterpret_cast<double *>(base + L.norms);
+    const double nu = sa.opt.loss == 2 ? INFINITY : sa.C;
+    *done = false;
+    KDCD_HIP_TRY(launch_fill_i32(status, 0, 1, sa.st));
+    KDCD_HIP_TRY(launch_validate(sa.idx, sa.H, A->m, sa.y, sa.alpha, A->m, 0, nu, status, sa.st));
+    if (sa.kernel->kind == KDCD_KERNEL_RBF) KDCD_HIP_TRY(launch_norms(A, norms, sa.st));
+    KDCD_HIP_TRY(launch_fill_i32(reinterpret_cast<int32_t *>(base + o_slots), kPersistEmptyWord,
+                                 6 * groups * sa.s, sa.st));
+    KDCD_HIP_TRY(hipMemcpyAsync(base + o_save, sa.alpha, sizeof(double) * (size_t)A->m,
+                                hipMemcpyDeviceToDevice, sa.st));
+    SvmPersistArgs pa{};
+    pa.A = A;
+    pa.y = sa.y;
+    pa.norms = norms;
+    pa.kp = to_params(sa.kernel);
+    pa.nu = nu;
+    pa.omega = sa.opt.loss == 2 ? 1.0 / (2.0 * sa.C) : 0.0;
+    pa.s = sa.s;
+    pa.H = sa.H;
+    pa.idx = sa.idx;
+    pa.alpha = sa.alpha;
+    pa.trace = sa.opt.trace;
+    pa.slots = reinterpret_cast<uint64_t *>(base + o_slots);
+    pa.status = status;
+    if (launch_svm_persist(pa, groups, sa.st) != hipSuccess) {   // not all workgroups fit
+        (void)hipGetLastError();
+        return KDCD_OK;
+    }
+    const kdcd_status rc = read_status(status, sa.st);
+    if ((int32_t)rc == kPersistGaveUp) {
+        KDCD_HIP_TRY(hipMemcpyAsync(sa.alpha, base + o_save, sizeof(double) * (size_t)A->m,
+                                    hipMemcpyDeviceToDevice, sa.st));
+        return KDCD_OK;
+    }
+    *done = true;
+    return rc;
+}
+
 kdcd_status run_solve(const SolveArgs &sa)
 {
     kdcd_status rc = check_monitor(sa.A, sa.opt);
@@ -1454,8 +1522,23 @@ kdcd_status run_solve(const SolveArgs &sa)
                              return enqueue_solve(g, L, base, off);
                          });
     }
+    const int64_t persist = persist_groups(sa);
+    size_t o_save = 0, o_slots = 0;
+    if (persist > 0) {
+        o_save = L.total;
+        o_slots = o_save + align256(sizeof(double) * (size_t)sa.A->m);
+        L.total = o_slots + align256(sizeof(uint64_t) * (size_t)(3 * persist * sa.s));
+    }
     Workspace ws;
     if ((rc = acquire(ws, L, &sa.opt, sa.st)) != KDCD_OK) return rc;
+    if (persist > 0) {
+        bool done = false;
+        rc = run_persist(sa, L, ws.base, o_save, o_slots, persist, &done);
+        if (rc != KDCD_OK || done) {
+            if (rc != KDCD_OK) (void)hipStreamSynchronize(sa.st);
+            return rc;
+        }
+    }
     SolveArgs sx = sa;
     if (sa.A->format == KDCD_CSR && sa.A->m > 0) {
         // the longest row (one reduction and a wait at the start of the call),
