@@ -194,6 +194,9 @@ struct KBlockArgs {
     // <= 0: the sb rows of S), W is then w_rows x sb; the batched launch ignores it
     int32_t w_row0 = 0;
     int32_t w_rows = 0;
+    // Gram-only FP64 launch of w_batch index blocks that lie back to back (block i:
+    // S + i sb, W + i w_rows sb)
+    int32_t w_batch = 1;
 };
 
 // K-RR lookahead (one problem, dense FP64, gathered Gram).  The recurrence of

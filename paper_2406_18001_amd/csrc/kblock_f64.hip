@@ -153,6 +153,10 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(OCC))) 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int total = n_tiles_n * (n_row_groups + n_w_tiles);
+    if (!BATCH && !LA && gridDim.y > 1) {        // Gram-only launch of several index blocks
+        S += (int64_t)blockIdx.y * sb;
+        W += (int64_t)blockIdx.y * w_rows * sb;
+    }
     // the leading workgroups of a lookahead launch are a multiple of 8, so
     // bid % 8 is still the XCD of the workgroup
     const int bid = LA ? (int)blockIdx.x - kLaLead : (int)blockIdx.x;
@@ -600,7 +604,7 @@ hipError_t launch_tiles(const KBlockArgs &a, hipStream_t st, int nprob = 0)
         return hipErrorInvalidValue;   // the caller checks lookahead_supported first
     const int64_t blocks = n_n * (groups + n_w) + (la ? kLaLead : 0);
     const LookaheadArgs lav = la ? *a.la : LookaheadArgs{};
-    dim3 grid((unsigned)blocks), block(64 * WM);
+    dim3 grid((unsigned)blocks, a.w_only && !BATCH ? (unsigned)a.w_batch : 1u), block(64 * WM);
     const size_t dyn = sizeof(double) * (size_t)((A->n % BK ? BN * BK : 0) +
                                                  (BATCH ? nprob * (BM + WM * BN) : 0));
 #define KDCD_LAUNCH_F(KIND, LA)                                                                  \

@@ -60,10 +60,16 @@ int64_t max_row_groups(const kdcd_matrix *A)
 // these widths add a round of workgroups.
 constexpr int64_t kGatherMinSB = 256;
 // Tile configurations (single problem, batched) of the FP64 Gram-only launches
-// that follow a low-precision product: 64 x 16 spreads an s*b-row Gram over the
-// most workgroups; with its long K loop and few tiles that launch is bound by
-// latency, not by the tile's MFMA rate.
-constexpr int32_t kGramCfg = 6, kGramBatchCfg = 0;
+// that follow a low-precision product.  One index block: 64 x 16 spreads an s*b-row
+// Gram over the most workgroups; with its long K loop and few tiles that launch is
+// bound by latency, not by the tile's MFMA rate.  A Gram needs only the indices, so
+// where the call has the memory the Grams of several blocks come from one launch
+// ahead of them, which fills the chip: 128 x 64 tiles.  20000 x 512, s*b = 512, rows
+// of two blocks: 25 us for one block's launch, 11 us a block ahead (200000 x 1024,
+// bf16, one block's rows: 31 and 12).
+constexpr int32_t kGramCfg = 6, kGramBatchCfg = 0, kGramAheadCfg = 5;
+constexpr int64_t kGramAhead = 16;              // blocks of one such launch, at most
+constexpr size_t kGramAheadBytes = 64u << 20;   // and their memory
 // Largest rank of a low-rank factor (Nystrom landmarks, columns of Phi).
 constexpr int64_t kMaxRank = 4096;
 
@@ -149,6 +155,8 @@ size_t lowp_elem_bytes(int32_t compute) { return compute == KDCD_F32 ? 4 : 2; }
 struct Layout {
     size_t status, norms, partial, r, W, Dinv, iota, hi, lo, normlow, pos, carry, panel, total;
     size_t panel_bytes;   // CSR: size of the sampled rows' panel region
+    size_t ahead;         // low precision: Grams of ahead_n blocks formed ahead (0: one by one)
+    int64_t ahead_n;
     // K-RR lookahead (la_ok): second row table and Gram, the kernel rows of the
     // previous block's coordinates, its summed updates and their coordinates
     bool la_ok;
@@ -170,6 +178,19 @@ void grow_panel(Layout &L, const kdcd_matrix *A, const kdcd_options *opt)
     L.panel = L.total;
     L.panel_bytes = csr_panel_full_bytes(A);
     L.total += align256(L.panel_bytes);
+}
+
+// Memory for low-precision Grams formed ahead, in a workspace of the call's own:
+// rows of `rows` index blocks against one.
+void grow_gram(Layout &L, int64_t sb, int64_t rows, int64_t n_outer, const kdcd_options &o)
+{
+    if (o.compute == KDCD_F64 || o.workspace) return;
+    const size_t one = sizeof(double) * (size_t)(rows * sb * sb);
+    const int64_t nb = std::min<int64_t>(std::min<int64_t>(kGramAhead, n_outer), (int64_t)(kGramAheadBytes / one));
+    if (nb < 2) return;
+    L.ahead = L.total;
+    L.ahead_n = nb;
+    L.total += align256(one * (size_t)nb);
 }
 
 void add_monitor(Layout &L, int64_t m, int64_t sbmax)
@@ -774,10 +795,10 @@ kdcd_status enqueue_lookahead_lowp(const SolveArgs &sa, const Layout &L, Workspa
     double *r = ws.at<double>(L.r);
     double *Dinv = ws.at<double>(L.Dinv);
     int32_t *P[2] = {ws.at<int32_t>(L.pos), ws.at<int32_t>(L.pos2)};
-    double *Wx = ws.at<double>(L.W2);
     double *Dc = ws.at<double>(L.la_dc);
     int32_t *Sc = ws.at<int32_t>(L.la_sc);
     const int64_t n_outer = (sa.H + sa.s - 1) / sa.s;
+    const int64_t sb_full = (int64_t)sa.s * sa.b;
     auto block = [&](int64_t k, int32_t &sk, int32_t &sb) -> const int32_t * {
         const int64_t done = k * sa.s;
         sk = (int32_t)std::min<int64_t>(sa.s, sa.H - done);
@@ -787,27 +808,39 @@ kdcd_status enqueue_lookahead_lowp(const SolveArgs &sa, const Layout &L, Workspa
     auto trace_of = [&](int64_t k) -> double * {
         return sa.opt.trace ? sa.opt.trace + k * sa.s * sa.b : nullptr;
     };
+    // rows of block k - 1 and of block k against block k: one buffer, or with
+    // memory for Grams ahead one of ahead_n (block k >= 1: number (k - 1) mod ahead_n)
+    auto buffer_of = [&](int64_t k) -> double * {
+        if (L.ahead_n < 2 || k == 0) return ws.at<double>(L.W2);
+        return ws.at<double>(L.ahead) + ((k - 1) % L.ahead_n) * 2 * sb_full * sb_full;
+    };
     // the Gram of block k (after the QX rows of block k - 1, when there is one)
     auto gram_of = [&](int64_t k) -> double * {
         int32_t skk = 0, sbk = 0, skp = 0, sbp = 0;
         block(k, skk, sbk);
         if (k > 0) block(k - 1, skp, sbp);
-        return Wx + (int64_t)sbp * sbk;
+        return buffer_of(k) + (int64_t)sbp * sbk;
     };
     auto gram_launch = [&](int64_t k) -> kdcd_status {
         int32_t skk = 0, sbk = 0, skp = 0, sbp = 0;
         const int32_t *Sk = block(k, skk, sbk);
         if (k > 0) block(k - 1, skp, sbp);
+        int64_t ahead = 1;
+        if (L.ahead_n > 1 && k > 0 && sbk == sb_full) {
+            if ((k - 1) % L.ahead_n != 0) return KDCD_OK;      // formed with an earlier block's
+            ahead = std::min<int64_t>(L.ahead_n, sa.H / sa.s - k);   // whole blocks from k on
+        }
         KBlockArgs w = kb;
         w.compute = KDCD_F64;
         w.w_only = 1;
-        w.cfg = kGramCfg;
+        w.cfg = ahead > 1 ? kGramAheadCfg : kGramCfg;
+        w.w_batch = (int32_t)ahead;
         w.U = nullptr;
         w.pos = nullptr;
         w.la = nullptr;
         w.S = Sk;
         w.sb = sbk;
-        w.W = Wx;
+        w.W = buffer_of(k);
         w.w_row0 = -sbp;          // block k - 1's indices precede block k's in idx
         w.w_rows = sbp + sbk;
         KDCD_HIP_TRY(launch_kblock_f64(w, st));
@@ -822,7 +855,7 @@ kdcd_status enqueue_lookahead_lowp(const SolveArgs &sa, const Layout &L, Workspa
         KBlockArgs t = kb;
         t.S = S0;
         t.sb = sb0;
-        t.W = Wx;
+        t.W = ws.at<double>(L.W2);
         t.pos = P[0];
         t.prevS = nullptr;
         t.prev_sb = 0;
@@ -862,7 +895,7 @@ kdcd_status enqueue_lookahead_lowp(const SolveArgs &sa, const Layout &L, Workspa
         fd.dup_W = Wk;
         fd.m = A->m;
         if (k > 0) {
-            fd.la_QX = Wx;            // block k - 1's rows against block k's columns
+            fd.la_QX = buffer_of(k);  // block k - 1's rows against block k's columns
             fd.la_Dc = Dc;
             fd.la_Sc = Sc;
             fd.la_sb = sbp;
@@ -1031,6 +1064,7 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
         kb.prev_sb = kb.sb;
         kb.S = S;
         kb.sb = sb;
+        double *Wk = L.ahead_n > 1 ? ws.at<double>(L.ahead) + ((k - R.k_begin) % L.ahead_n) * sb_full * sb_full : W;
         // K-RR with a gathered Gram: the finish launch copies the repeated rows
         // and each recurrence prepares the row -> position table of the next
         // block, so only the first block needs the separate update launch
@@ -1051,18 +1085,29 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
             const hipError_t e = launch_kblock_csr(kb, st);
             timer.disarm();
             KDCD_HIP_TRY(e);
-        } else if (product_only && A->format == KDCD_DENSE) {
-            // low-precision product timed in its own dispatch; the FP64 Gram
-            // launch after it is not timed
-            if (!sampled || k % 8 == 0) timer.arm(0);
-            const hipError_t e = launch_kblock_mixed(kb, st);
+        } else if (A->format == KDCD_DENSE) {
+            // low-precision product, timed in its own dispatch when only the
+            // product is, and the FP64 Gram: of this block, or (with the memory) of
+            // the next ahead_n whole blocks of the range at once
+            if (!product_only) timer.begin(0, st);
+            else if (!sampled || k % 8 == 0) timer.arm(0);
+            hipError_t e = launch_kblock_mixed(kb, st);
             timer.disarm();
             KDCD_HIP_TRY(e);
             KBlockArgs w = kb;
             w.compute = KDCD_F64;
             w.w_only = 1;
             w.cfg = kGramCfg;
-            KDCD_HIP_TRY(launch_kblock_f64(w, st));
+            w.U = nullptr;       // the stored kernel block is the low-precision product's
+            w.W = Wk;
+            bool formed = false;
+            if (L.ahead_n > 1 && sb == sb_full) {
+                formed = (k - R.k_begin) % L.ahead_n != 0;
+                w.w_batch = (int32_t)std::min<int64_t>(L.ahead_n, std::min<int64_t>(k_end, sa.H / sa.s) - k);
+                if (w.w_batch > 1) w.cfg = kGramAheadCfg;
+            }
+            if (!formed) KDCD_HIP_TRY(launch_kblock_f64(w, st));
+            if (!product_only) timer.end(0, st);
         } else {
             timer.begin(0, st);
             KDCD_HIP_TRY(launch_kblock(kb, st));
@@ -1074,14 +1119,14 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
         fd.groups = (int32_t)groups;
         fd.partial[0] = partial;
         fd.r[0] = r;
-        fd.W[0] = W;
+        fd.W[0] = Wk;
         fd.Dinv[0] = Dinv;
         fd.inv_lambda[0] = svm ? 0.0 : 1.0 / sa.lambda;
         fd.stop = stop;
         if (fused) {
             fd.dup_S = S;
             fd.dup_pos = kb.pos;
-            fd.dup_W = W;
+            fd.dup_W = Wk;
             fd.m = A->m;
         }
         if (!product_only) timer.arm(1);
@@ -1095,7 +1140,7 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
         if (svm) {
             KsvmRecurDesc kd{};
             kd.r[0] = r;
-            kd.W[0] = W;
+            kd.W[0] = Wk;
             kd.y[0] = sa.y;
             kd.alpha[0] = sa.alpha;
             kd.trace[0] = tr;
@@ -1109,7 +1154,7 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
         } else {
             KrrRecurDesc rd{};
             rd.r[0] = r;
-            rd.W[0] = W;
+            rd.W[0] = Wk;
             rd.Dinv[0] = Dinv;
             rd.y[0] = sa.y;
             rd.alpha[0] = sa.alpha;
@@ -1493,6 +1538,8 @@ kdcd_status run_solve(const SolveArgs &sa)
     if (rc != KDCD_OK) return rc;
     Layout L = make_layout(sa.problem, sa.A, sa.kernel, sa.b, sa.s, sa.opt.compute);
     grow_panel(L, sa.A, &sa.opt);
+    // (the lookahead loop's Gram launches take the rows of two blocks)
+    grow_gram(L, (int64_t)sa.s * sa.b, L.la_ok ? 2 : 1, (sa.H + sa.s - 1) / sa.s, sa.opt);
     if (sa.opt.monitor_every > 0) {
         add_monitor(L, sa.A->m, (int64_t)sa.s * sa.b);
         // the lookahead loop keeps two stored kernel blocks (not in a caller's
