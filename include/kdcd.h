@@ -153,7 +153,7 @@ typedef struct {
  * after it (low precision), and the finish pass of block k+1 adds those rows
  * times the updates to r_{k+1} and the updates to alpha, which is Algorithm
  * 4's r_{k+1} = U_{k+1}^T alpha up to rounding.  Used by default
- * when 2 m n s b >= 4e9 (the product then outlasts the recurrence it hides);
+ * where a rule on m, n, s, b and the compute type expects it to be the faster;
  * KDCD_FLAG_LOOKAHEAD asks for it at any size, KDCD_FLAG_SERIAL never.  Calls
  * that KDCD_FLAG_GRAPH replays by windows run the serial loop.
  */

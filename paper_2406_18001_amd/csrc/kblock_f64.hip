@@ -144,8 +144,8 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(OCC))) 
         if (blockIdx.x < kLaLead) {
             if (blockIdx.x == 0 && la.sb > 0) {
                 char *smem = reinterpret_cast<char *>(&Bs[0][0]);
-                if (la.b == 8) la_recur<NT, 8>(la, smem);
-                else la_recur<NT, 0>(la, smem);
+                if (la.b > 4) la_recur<NT, 8>(la, smem);
+                else la_recur<NT, 4>(la, smem);
             }
             return;
         }

@@ -116,8 +116,8 @@ void kblock_lowp_kernel(
         if (blockIdx.x < kLaLead) {
             if (blockIdx.x == 0 && la.sb > 0) {
                 char *smem = reinterpret_cast<char *>(&As[0][0][0]);
-                if (la.b == 8) la_recur<kThreads, 8>(la, smem);
-                else la_recur<kThreads, 0>(la, smem);
+                if (la.b > 4) la_recur<kThreads, 8>(la, smem);
+                else la_recur<kThreads, 4>(la, smem);
             }
             return;
         }

@@ -99,8 +99,8 @@ void kblock_mixed_kernel(
         if (blockIdx.x < kLaLead) {
             if (blockIdx.x == 0 && la.sb > 0) {
                 char *smem = reinterpret_cast<char *>(&As[0][0][0]);
-                if (la.b == 8) la_recur<NT, 8>(la, smem);
-                else la_recur<NT, 0>(la, smem);
+                if (la.b > 4) la_recur<NT, 8>(la, smem);
+                else la_recur<NT, 4>(la, smem);
             }
             return;
         }

@@ -569,10 +569,23 @@ struct SolveRange {
     const int32_t *S_base = nullptr;
 };
 
-// Work (2 m n s b flops per product) from which the lookahead loop is the
-// default: the product then takes well over 100 us, several times the
-// recurrence it hides.
-constexpr double kLaMinFlops = 4e9;
+// Whether the lookahead loop is the faster one (us an index block): its launch lasts
+// as long as the longer of the product and a recurrence that steps through the s
+// blocks, the other loop's as long as the product, the recurrence of its own launch
+// and a few us of gaps.  20000 x 512, lookahead / not: FP64 b = 8,
+// s = 64: 199 / 226, b = 1, s = 300: 158 / 189, s = 500: 263 / 256; bf16x3 91 / 107,
+// 109 / 85, 184 / 133; 8000 x 128, b = 4, s = 128: FP64 73 / 77, bf16x3 72 / 60;
+// 5000 x 256, bf16, b = 8, s = 64: 59 / 60.
+bool lookahead_pays(int64_t m, int64_t n, int32_t b, int32_t s, int32_t compute)
+{
+    const double flops = 2.0 * (double)m * (double)n * (double)s * (double)b;
+    const double rate = compute == KDCD_F64 ? 5e7 : compute == KDCD_F32 ? 1e8 : compute == KDCD_BF16X3 ? 1.8e8 : 8e8;
+    const double product = 4.0 + flops / rate;
+    const double step = b > 4 ? 0.56 : (compute == KDCD_F64 ? 0.5 : 0.36);
+    // (past 512 threads the recurrence's launch is not pipelined)
+    const double own = (double)s * (0.06 + 0.043 * b) * (krr_recur_threads(b, s) > 512 ? 2.5 : 1.0);
+    return 4.0 + (double)s * step < product + own + 5.0;
+}
 
 // Whether a K-RR solve runs the lookahead loop (see LookaheadArgs): dense FP64
 // with a gathered Gram, b <= 8, 256 <= s*b <= 512, whole product tiles along
@@ -597,7 +610,7 @@ bool lookahead_use(const SolveArgs &sa, const Layout &L, const KBlockArgs &kb,
     const int64_t sb_full = (int64_t)sa.s * sa.b;
     if (sb_full > (int64_t)kLaEPT * 256) return false;
     if (sa.opt.flags & KDCD_FLAG_LOOKAHEAD) return true;
-    return 2.0 * (double)A->m * (double)A->n * (double)sb_full >= kLaMinFlops;
+    return lookahead_pays(A->m, A->n, sa.b, sa.s, sa.opt.compute);
 }
 
 // The lookahead loop of a K-RR solve.  Per outer iteration k: the finish pass
