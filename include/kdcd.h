@@ -562,7 +562,8 @@ kdcd_status kdcd_tune_save(const char *path);
 kdcd_status kdcd_tune_load(const char *path);
 
 /* Destroy every graph cached by KDCD_FLAG_GRAPH calls and free the
- * workspaces they own (no call may be running). */
+ * workspaces they own (no call may be running), and return the freed
+ * workspaces that the library keeps for later calls (at most 1 GiB a device). */
 void kdcd_graph_cache_clear(void);
 
 /* Device workspace a solve needs (problem: 0 = K-SVM, 1 = K-RR). */

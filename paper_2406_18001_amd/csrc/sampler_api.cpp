@@ -186,8 +186,8 @@ kdcd_status kdcd_sampler_select(const float *keys, int64_t m, int32_t s, double 
         return KDCD_ERR_INVALID_ARG;
     const hipStream_t st = (hipStream_t)stream;
     void *ws = nullptr;
-    const size_t bytes = select_workspace_bytes(m) + 256;
-    if (hipMallocAsync(&ws, bytes, st) != hipSuccess) return KDCD_ERR_ALLOC;
+    size_t bytes = select_workspace_bytes(m) + 256;
+    if (workspace_alloc(&ws, &bytes, st) != hipSuccess) return KDCD_ERR_ALLOC;
     int32_t *status = static_cast<int32_t *>(ws);
     SelectArgs a{};
     a.ws = select_workspace(static_cast<char *>(ws) + 256, m);
@@ -206,8 +206,8 @@ kdcd_status kdcd_sampler_select(const float *keys, int64_t m, int32_t s, double 
         launch_select(a, st) != hipSuccess ||
         hipMemcpyAsync(&hs, status, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess)
         rc = KDCD_ERR_HIP;
-    (void)hipFreeAsync(ws, st);
     if (hipStreamSynchronize(st) != hipSuccess) rc = KDCD_ERR_HIP;
+    workspace_free(ws, bytes, st);
     if (rc == KDCD_OK) rc = (kdcd_status)hs;
     return rc;
 }

@@ -254,13 +254,13 @@ Layout make_layout(int32_t problem, const kdcd_matrix *A, const kdcd_kernel *ker
 // Device workspace: caller-provided or allocated on the stream.
 struct Workspace {
     char *base = nullptr;
-    bool owned = false;
+    size_t owned = 0;      // bytes, 0: the caller's
     hipStream_t st = nullptr;
     ~Workspace()
     {
         if (owned && base) {
-            (void)hipFreeAsync(base, st);
             (void)hipStreamSynchronize(st);
+            workspace_free(base, owned, st);
         }
     }
     template <class T> T *at(size_t off) const { return reinterpret_cast<T *>(base + off); }
@@ -276,15 +276,112 @@ kdcd_status acquire(Workspace &ws, const Layout &L, const kdcd_options *opt, hip
         return KDCD_OK;
     }
     void *p = nullptr;
-    if (hipMallocAsync(&p, L.total, st) != hipSuccess || !p) return KDCD_ERR_ALLOC;
+    size_t bytes = L.total;
+    if (workspace_alloc(&p, &bytes, st) != hipSuccess || !p) return KDCD_ERR_ALLOC;
     ws.base = static_cast<char *>(p);
-    ws.owned = true;
+    ws.owned = bytes;
     return KDCD_OK;
 }
 
 }  // namespace
 
 namespace kdcd {
+
+// Freed workspaces, kept for later calls: at most kKeepBlocks and kKeepBytes a device,
+// the oldest go first; kdcd_graph_cache_clear and a failed allocation return them all.  A
+// block comes back only after its call has synchronised its stream, so it is idle and
+// any thread and stream may take it.  Allocated and freed by each call, a workspace of
+// up to 64 MB cost 40 us a call and a larger one 300.
+namespace {
+constexpr int kKeepDevices = 64;
+constexpr size_t kKeepBlocks = 16, kKeepBytes = (size_t)1 << 30;
+struct Kept {
+    std::mutex mu;
+    std::vector<std::pair<void *, size_t>> blocks[kKeepDevices];   // oldest first
+};
+Kept &kept()
+{
+    static Kept *k = new Kept;   // never destroyed: the runtime may go first
+    return *k;
+}
+int stream_device(hipStream_t st)
+{
+    int dev = -1;
+    if ((st ? hipStreamGetDevice(st, &dev) : hipGetDevice(&dev)) != hipSuccess) {
+        (void)hipGetLastError();
+        return -1;
+    }
+    return dev < kKeepDevices ? dev : -1;
+}
+}  // namespace
+
+hipError_t workspace_alloc(void **ptr, size_t *bytes, hipStream_t st)
+{
+    const int dev = stream_device(st);
+    const size_t need = *bytes;
+    if (dev >= 0) {
+        Kept &k = kept();
+        std::lock_guard<std::mutex> lk(k.mu);
+        auto &b = k.blocks[dev];
+        auto best = b.end();
+        for (auto x = b.begin(); x != b.end(); ++x)
+            if (x->second >= need && (best == b.end() || x->second < best->second)) best = x;
+        // (a small call leaves a large block to a large one)
+        if (best != b.end() && best->second <= 4 * need + ((size_t)4 << 20)) {
+            *ptr = best->first;
+            *bytes = best->second;
+            b.erase(best);
+            return hipSuccess;
+        }
+    }
+    // rounded up, so that a call a little larger finds the block too
+    size_t step = (size_t)64 << 10;
+    while (step * 16 < need) step *= 2;
+    *bytes = (need + step - 1) / step * step;
+    hipError_t e = hipMallocAsync(ptr, *bytes, st);
+    if (e == hipSuccess && *ptr) return e;
+    (void)hipGetLastError();
+    workspace_trim();
+    *bytes = need;
+    return hipMallocAsync(ptr, need, st);
+}
+
+void workspace_free(void *ptr, size_t bytes, hipStream_t st)
+{
+    const int dev = stream_device(st);
+    std::vector<void *> drop;
+    if (dev < 0 || bytes > kKeepBytes) {
+        drop.push_back(ptr);
+    } else {
+        Kept &k = kept();
+        std::lock_guard<std::mutex> lk(k.mu);
+        auto &b = k.blocks[dev];
+        b.emplace_back(ptr, bytes);
+        size_t sum = 0;
+        for (const auto &x : b) sum += x.second;
+        while (b.size() > kKeepBlocks || sum > kKeepBytes) {
+            sum -= b.front().second;
+            drop.push_back(b.front().first);
+            b.erase(b.begin());
+        }
+    }
+    for (void *p : drop) (void)hipFreeAsync(p, st);
+    if (!drop.empty()) (void)hipStreamSynchronize(st);
+}
+
+void workspace_trim()
+{
+    Kept &k = kept();
+    std::lock_guard<std::mutex> lk(k.mu);
+    bool any = false;
+    for (auto &b : k.blocks) {
+        for (const auto &x : b) (void)hipFree(x.first);
+        any = any || !b.empty();
+        b.clear();
+    }
+    if (any) (void)hipDeviceSynchronize();   // the device's pool returns it then
+}
+
 ArmedEvents &armed_events()
 {
     static thread_local ArmedEvents ev{nullptr, nullptr};
@@ -1665,6 +1762,7 @@ void kdcd_graph_cache_clear(void)
     std::lock_guard<std::mutex> lk(c.mu);
     for (auto &e : c.entries) drop_entry(e);
     c.entries.clear();
+    workspace_trim();
 }
 
 kdcd_status kdcd_ksvm_solve(const kdcd_matrix *A, const double *y, const kdcd_kernel *kernel,
