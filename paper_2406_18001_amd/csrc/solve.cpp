@@ -24,7 +24,8 @@ hipError_t launch_kblock_csr(const KBlockArgs &a, hipStream_t st);
 int64_t kblock_csr_row_groups(const KBlockArgs &a);
 int64_t kblock_csr_max_row_groups(const kdcd_matrix *A);
 hipError_t launch_convert_lowp(const kdcd_matrix *A, int32_t compute, void *hi, void *lo,
-                               int64_t ldlow, float *normlow, hipStream_t st);
+                               int64_t ldlow, float *normlow, double *norms,
+                               hipStream_t st);
 int krr_recur_threads(int32_t b, int32_t sk);
 int32_t lowrank_zinit_chunks();
 size_t lowrank_part_bytes();
@@ -525,18 +526,25 @@ struct SolveArgs {
     int64_t csr_max_row = -1;   // CSR: longest row of A, when measured (-1: unknown)
 };
 
+// Whether prepare_lowp's copy makes the FP64 norms as well (no pass of their own).
+bool lowp_makes_norms(const kdcd_matrix *A, int32_t compute)
+{
+    return compute != KDCD_F64 && A->format == KDCD_DENSE;
+}
+
 kdcd_status prepare_lowp(const KBlockArgs &base, const Layout &L, Workspace &ws, hipStream_t st,
                          KBlockArgs &a, bool convert = true)
 {
     a = base;
-    if (base.compute == KDCD_F64 || base.A->format != KDCD_DENSE) return KDCD_OK;
+    if (!lowp_makes_norms(base.A, base.compute)) return KDCD_OK;
     a.Alow = ws.at<void>(L.hi);
     a.Alow2 = ws.at<void>(L.lo);
     a.ldlow = L.ldlow;
     a.normlow = ws.at<float>(L.normlow);
     if (convert)
         KDCD_HIP_TRY(launch_convert_lowp(base.A, base.compute, ws.at<void>(L.hi), ws.at<void>(L.lo),
-                                         L.ldlow, ws.at<float>(L.normlow), st));
+                                         L.ldlow, ws.at<float>(L.normlow),
+                                         base.kp.kind == KDCD_KERNEL_RBF ? ws.at<double>(L.norms) : nullptr, st));
     return KDCD_OK;
 }
 
@@ -1100,7 +1108,8 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
         if (A->format == KDCD_CSR) KDCD_HIP_TRY(launch_validate_csr(A, status, st));
         KDCD_HIP_TRY(launch_validate(sa.idx, sa.H * sa.b, A->m, sa.y, sa.alpha, A->m, sa.problem,
                                      nu, status, st));
-        if (sa.kernel->kind == KDCD_KERNEL_RBF) KDCD_HIP_TRY(launch_norms(A, norms, st));
+        if (sa.kernel->kind == KDCD_KERNEL_RBF && !lowp_makes_norms(A, sa.opt.compute))
+            KDCD_HIP_TRY(launch_norms(A, norms, st));
     }
 
     KBlockArgs base{};
@@ -1878,7 +1887,7 @@ kdcd_status kdcd_batch_solve(const kdcd_matrix *A, const kdcd_kernel *kernel, in
         KDCD_HIP_TRY(launch_validate(idx, 0, A->m, q.y, q.alpha, A->m, q.problem == 0 ? 0 : 1, nu,
                                      status, st));
     }
-    if (rbf) KDCD_HIP_TRY(launch_norms(A, norms, st));
+    if (rbf && !lowp_makes_norms(A, o.compute)) KDCD_HIP_TRY(launch_norms(A, norms, st));
 
     KBlockArgs base{};
     base.A = A;
@@ -2475,7 +2484,7 @@ kdcd_status kdcd_kernel_rhs(const kdcd_matrix *A, const kdcd_kernel *kernel, con
     KDCD_HIP_TRY(launch_fill_i32(status, 0, 1, st));
     if (A->format == KDCD_CSR) KDCD_HIP_TRY(launch_validate_csr(A, status, st));
     KDCD_HIP_TRY(launch_validate(S, sb, A->m, nullptr, nullptr, 0, 0, 0.0, status, st));
-    if (kernel->kind == KDCD_KERNEL_RBF) KDCD_HIP_TRY(launch_norms(A, norms, st));
+    if (kernel->kind == KDCD_KERNEL_RBF && !lowp_makes_norms(A, compute)) KDCD_HIP_TRY(launch_norms(A, norms, st));
     KBlockArgs base{};
     base.A = A;
     base.S = S;
