@@ -189,6 +189,7 @@ struct KBlockArgs {
     // -1; a chunk of sampled rows that cannot exceed the panel then skips the
     // broadcast launch that would only run for an overflowing chunk
     int64_t csr_max_row = -1;
+    bool csr_built = false;  // the first chunk's dense-head panel was built ahead
     // dense single-problem FP64 product: tile configuration, resolved once by
     // the caller together with the row-group count the finish pass sums
     // (-1: looked up in the tuning table at launch)
@@ -399,6 +400,22 @@ hipError_t launch_rho_init(const double *Ka, const double *y, const double *alph
 // r[j] += sum over the first occurrences t in prevS of X[t][j] * beta(prevS_t),
 hipError_t launch_finish(const FinishDesc &d, int32_t sb, int32_t b, int32_t sk, double mdbl,
                          int32_t *status, hipStream_t st);
+// A dense-head panel to build (see csr_head.hpp), and whether the CSR product of `a`
+// reads one.
+struct CsrBuildArgs {
+    const int64_t *row_ptr;
+    const int32_t *col_idx;
+    const double *val;
+    int64_t nnz, n;
+    const int32_t *S;
+    int32_t nj;
+    void *panel;
+};
+bool csr_takes_head(const KBlockArgs &a);
+constexpr int32_t kCsrHeadRows = 32;   // sampled rows of a chunk
+// The recurrence of a block of s <= 64 with the panel of the next block in its launch.
+hipError_t launch_ksvm_recur_build(const KsvmRecurDesc &d, const int32_t *S, int32_t sb, int64_t m, int32_t *status,
+                                   const CsrBuildArgs &next, hipStream_t st);
 hipError_t launch_ksvm_recur(const KsvmRecurDesc &d, int32_t nprob, const int32_t *S, int32_t sb,
                              int64_t m, int32_t *status, hipStream_t st);
 hipError_t launch_krr_recur(const KrrRecurDesc &d, int32_t nprob, const int32_t *S, int32_t b,

@@ -21,6 +21,7 @@
 // Both scatter alpha_{S_t} += update in t order: the last occurrence of each
 // coordinate writes alpha_0 + (its running sum), so duplicates accumulate.
 #include "common.hpp"
+#include "csr_head.hpp"
 #include "dcd_step.hpp"
 
 namespace kdcd {
@@ -87,27 +88,34 @@ __device__ __forceinline__ void stage_diag(const double *__restrict__ W, int32_t
 }
 
 // K-SVM recurrence.  NT threads (512 covers sb <= 512, 1024 covers sb <= 1024);
-// PF = W values of the next fold-in phase prefetched into registers.
+// PF = W values of the next fold-in phase prefetched into registers.  ONE: sb <= 64,
+// one panel and nothing to fold in.
 template <int NT>
-__global__ __launch_bounds__(NT) void ksvm_recur_kernel(const KsvmRecurDesc D,
-                                                        const int32_t *__restrict__ S, int32_t sb,
-                                                        int64_t m, int32_t *status)
+struct KsvmLds {
+    double Wd[2][64 * 64];
+    double th_l[kMaxSB + 64];       // padded: entries >= sb hold 0 / -1
+    double y_l[kMaxSB + 64];
+    __align__(16) int32_t S_l[kMaxSB + 64];
+    int32_t hkeys[kHashSlots], hidx[kHashSlots];
+};
+template <int NT, bool ONE>
+__device__ __forceinline__ void ksvm_recur(KsvmLds<NT> &lds, const KsvmRecurDesc &D, int pb,
+                                           const int32_t *__restrict__ S, int32_t sb, int64_t m, int32_t *status)
 {
     if (D.stop && *D.stop) return;             // converged: nothing more to do
-    // problem of this workgroup (one workgroup per problem of a batch)
-    const int pb = blockIdx.x;
     const double *__restrict__ r = D.r[pb];
     const double *__restrict__ W = D.W[pb];
     const double *__restrict__ y = D.y[pb];
     double *__restrict__ alpha = D.alpha[pb];
     double *__restrict__ trace = D.trace[pb];
     const double nu = D.nu[pb], omega = D.omega[pb];
-    constexpr int PF = NT <= 512 ? 64 : 32;
-    __shared__ double Wd[2][64 * 64];
-    __shared__ double th_l[kMaxSB + 64];       // padded: entries >= sb hold 0 / -1
-    __shared__ double y_l[kMaxSB + 64];
-    __shared__ __align__(16) int32_t S_l[kMaxSB + 64];
-    __shared__ int32_t hkeys[kHashSlots], hidx[kHashSlots];
+    constexpr int PF = ONE ? 1 : (NT <= 512 ? 64 : 32);
+    auto &Wd = lds.Wd;
+    auto &th_l = lds.th_l;
+    auto &y_l = lds.y_l;
+    auto &S_l = lds.S_l;
+    auto &hkeys = lds.hkeys;
+    auto &hidx = lds.hidx;
     const int j = threadIdx.x, lane = j & 63, wid = j >> 6;
     const bool act = j < sb;
     const int64_t Sj = act ? clampi(S[j], 0, m - 1) : -1;
@@ -126,12 +134,12 @@ __global__ __launch_bounds__(NT) void ksvm_recur_kernel(const KsvmRecurDesc D,
     lds_barrier();
     const int hslot = act ? lastocc_insert(hkeys, hidx, (int32_t)Sj, j) : 0;
 
-    const int npanels = (sb + 63) / 64;
+    const int npanels = ONE ? 1 : (sb + 63) / 64;
     for (int p = 0; p < npanels; ++p) {
         const int P0 = p * 64;
         const int plen = (sb - P0) < 64 ? (sb - P0) : 64;
         const int buf = p & 1;
-        const bool later = act && wid > p;
+        const bool later = !ONE && act && wid > p;
         double wpre[PF];
         if (later) {
 #pragma unroll
@@ -179,6 +187,34 @@ __global__ __launch_bounds__(NT) void ksvm_recur_kernel(const KsvmRecurDesc D,
         if (!isfinite(nv)) set_status(status, KDCD_ERR_NONFINITE);
         if (last) alpha[Sj] = nv;
         if (trace) trace[j] = theta;
+    }
+}
+
+// One workgroup per problem of a batch.
+template <int NT>
+__global__ __launch_bounds__(NT) void ksvm_recur_kernel(const KsvmRecurDesc D, const int32_t *__restrict__ S,
+                                                        int32_t sb, int64_t m, int32_t *status)
+{
+    __shared__ KsvmLds<NT> lds;
+    ksvm_recur<NT, false>(lds, D, blockIdx.x, S, sb, m, status);
+}
+
+// The recurrence of an index block of a CSR problem (sb <= 64) and, in a second
+// workgroup, the dense-head panel of the next block's first chunk, which needs only
+// its indices: 12 us a block no longer in the way (100000 rows of 50, s = 32: 9.2 for
+// the recurrence and 11.9 for the panel; both in 12.5).
+constexpr int RB_NT = 512;                     // threads of the recurrence
+__global__ __launch_bounds__(HD_BUILD_NT) void ksvm_recur_build_kernel(const KsvmRecurDesc D,
+                                                                       const int32_t *__restrict__ S, int32_t sb,
+                                                                       int64_t m, int32_t *status, const CsrBuildArgs B)
+{
+    constexpr size_t BYTES = sizeof(HeadBuildLds) > sizeof(KsvmLds<RB_NT>) ? sizeof(HeadBuildLds) : sizeof(KsvmLds<RB_NT>);
+    __shared__ __align__(16) char smem[BYTES];
+    if (blockIdx.x == 1) {
+        csr_panel_build(*reinterpret_cast<HeadBuildLds *>(smem), B.row_ptr, B.col_idx, B.val, m, B.nnz, B.S, B.nj,
+                        B.n, B.panel);
+    } else if (threadIdx.x < RB_NT) {          // (the other waves end: no barrier counts them)
+        ksvm_recur<RB_NT, true>(*reinterpret_cast<KsvmLds<RB_NT> *>(smem), D, 0, S, sb, m, status);
     }
 }
 
@@ -519,6 +555,14 @@ hipError_t launch_ksvm_recur(const KsvmRecurDesc &d, int32_t nprob, const int32_
     else
         KDCD_TIMED_LAUNCH((ksvm_recur_kernel<1024>), dim3(nprob), dim3(1024), 0, st, d, S, sb, m,
                           status);
+    return hipGetLastError();
+}
+
+hipError_t launch_ksvm_recur_build(const KsvmRecurDesc &d, const int32_t *S, int32_t sb, int64_t m, int32_t *status,
+                                   const CsrBuildArgs &next, hipStream_t st)
+{
+    if (sb > 64 || next.nj > HD_NJ) return hipErrorInvalidValue;
+    KDCD_TIMED_LAUNCH(ksvm_recur_build_kernel, dim3(2), dim3(HD_BUILD_NT), 0, st, d, S, sb, m, status, next);
     return hipGetLastError();
 }
 

@@ -1266,8 +1266,19 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
             kd.nu[0] = nu;
             kd.omega[0] = omega;
             kd.stop = stop;
+            // the next block's dense-head panel needs only its indices: built beside
+            // this recurrence when the block and the next are of s <= 64
+            const int32_t *Sn = S + sb;
+            const int32_t sbn = k + 1 < k_end ? (int32_t)std::min<int64_t>(sa.s, sa.H - (k + 1) * sa.s) : 0;
+            KBlockArgs nx = kb;
+            nx.S = Sn;
+            nx.sb = sbn;
+            kb.csr_built = A->format == KDCD_CSR && sb <= 64 && sbn > 0 && csr_takes_head(nx);
+            const CsrBuildArgs build{A->row_ptr, A->col_idx, A->values, A->nnz, A->n, Sn,
+                                     std::min(sbn, kCsrHeadRows), kb.csr_panel};
             if (!product_only) timer.arm(2);
-            const hipError_t e = launch_ksvm_recur(kd, 1, S, sb, A->m, status, st);
+            const hipError_t e = kb.csr_built ? launch_ksvm_recur_build(kd, S, sb, A->m, status, build, st)
+                                              : launch_ksvm_recur(kd, 1, S, sb, A->m, status, st);
             timer.disarm();
             KDCD_HIP_TRY(e);
         } else {
