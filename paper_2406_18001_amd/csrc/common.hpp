@@ -331,7 +331,12 @@ struct KsvmRecurDesc {
     double nu[kMaxProblems];
     double omega[kMaxProblems];
     const int32_t *stop;
+    // one problem, sb <= 16: non-null takes r from the product's partial sums
+    // ([groups][sb]) in the finish pass's order instead of r[0]
+    const double *partial;
+    int32_t groups;
 };
+constexpr int32_t kRecurSumSB = 16;
 
 struct KrrRecurDesc {
     const double *r[kMaxProblems];

@@ -1248,8 +1248,11 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
             fd.dup_W = Wk;
             fd.m = A->m;
         }
+        // K-SVM with few sampled rows and row groups: the recurrence takes the sum (a
+        // profiled solve keeps the pass it reports)
+        const bool recur_sums = svm && sb <= kRecurSumSB && groups <= 512 && !sa.opt.profile;
         if (!product_only) timer.arm(1);
-        {
+        if (!recur_sums) {
             const hipError_t e = launch_finish(fd, sb, sa.b, sk, (double)A->m, status, st);
             timer.disarm();
             KDCD_HIP_TRY(e);
@@ -1266,6 +1269,8 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
             kd.nu[0] = nu;
             kd.omega[0] = omega;
             kd.stop = stop;
+            kd.partial = recur_sums ? partial : nullptr;
+            kd.groups = (int32_t)groups;
             // the next block's dense-head panel needs only its indices: built beside
             // this recurrence when the block and the next are of s <= 64
             const int32_t *Sn = S + sb;
