@@ -11,24 +11,38 @@
 namespace kdcd {
 namespace {
 
-// One wave per row; lanes stride over the row (dense) or its stored entries (CSR).
+// A wave per ROWS consecutive rows; lanes stride over a row (dense) or its stored
+// entries (CSR, ROWS = 1).  Bound by memory: with many rows four a wave keep more
+// loads in flight and a quarter of the workgroups (500000 x 256: 230 us with one,
+// 166 with four), with few one a wave spreads them over the chip.
+constexpr int64_t kNormsManyRows = 65536;
+template <int ROWS>
 __global__ __launch_bounds__(256) void norms_kernel(const double *__restrict__ vals,
                                                     const int64_t *__restrict__ row_ptr,
                                                     int64_t m, int64_t n, int64_t ld,
                                                     double *__restrict__ norms)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t row = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * ROWS;
     if (row >= m) return;
-    double s = 0.0;
-    if (row_ptr) {
-        for (int64_t e = row_ptr[row] + lane; e < row_ptr[row + 1]; e += 64) s += vals[e] * vals[e];
+    double s[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) s[i] = 0.0;
+    if (ROWS == 1 && row_ptr) {
+        for (int64_t e = row_ptr[row] + lane; e < row_ptr[row + 1]; e += 64) s[0] += vals[e] * vals[e];
     } else {
-        const double *x = vals + row * ld;
-        for (int64_t k = lane; k < n; k += 64) s += x[k] * x[k];
+        const double *x[ROWS];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) x[i] = vals + (row + i < m ? row + i : m - 1) * ld;
+        for (int64_t k = lane; k < n; k += 64)
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i) s[i] += x[i][k] * x[i][k];
     }
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == 0) norms[row] = s;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        for (int off = 32; off > 0; off >>= 1) s[i] += __shfl_xor(s[i], off);
+        if (lane == 0 && row + i < m) norms[row + i] = s[i];
+    }
 }
 
 // problem 0 (K-SVM): y in {-1,+1}, 0 <= alpha <= nu; problem 1 (K-RR): finite y, alpha.
@@ -297,10 +311,13 @@ __global__ __launch_bounds__(256) void finish_kernel(const FinishDesc d, int32_t
 
 hipError_t launch_norms(const kdcd_matrix *A, double *norms, hipStream_t st)
 {
-    const unsigned blocks = (unsigned)((A->m + 3) / 4);
     const bool csr = A->format == KDCD_CSR;
-    hipLaunchKernelGGL(norms_kernel, dim3(blocks), dim3(256), 0, st, A->values,
-                       csr ? A->row_ptr : nullptr, A->m, A->n, A->ld, norms);
+    if (!csr && A->m >= kNormsManyRows)
+        hipLaunchKernelGGL(norms_kernel<4>, dim3((unsigned)((A->m + 15) / 16)), dim3(256), 0, st, A->values,
+                           nullptr, A->m, A->n, A->ld, norms);
+    else
+        hipLaunchKernelGGL(norms_kernel<1>, dim3((unsigned)((A->m + 3) / 4)), dim3(256), 0, st, A->values,
+                           csr ? A->row_ptr : nullptr, A->m, A->n, A->ld, norms);
     return hipGetLastError();
 }
 
