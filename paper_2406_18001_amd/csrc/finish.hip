@@ -274,6 +274,53 @@ __global__ __launch_bounds__(256) void finish_kernel(const FinishDesc d, int32_t
     const double inv_lambda = d.inv_lambda[k];
     const int bb = b * b;
     const int64_t base = (int64_t)j * b;
+    double *Dinv = d.Dinv[k];
+    if (b <= 16) {
+        // one wave, its elements in registers: a step is an LDS round trip and a
+        // division, without the barriers and index divisions of the form below
+        // (the pass at s b = 512, b = 16: 14.0 -> 9.9 us; four problems of a sweep:
+        // 34 -> 14; a whole block of 5000 x 128, b = 8, s = 16: 30.2 -> 26.9)
+        if (tid >= 64) return;
+        constexpr int EP = 4;
+        int l[EP], q[EP];
+        double cur[EP], rowk[EP], colk[EP];
+#pragma unroll
+        for (int i = 0; i < EP; ++i) {
+            if (64 * i >= bb) break;      // uniform
+            const int e = tid + 64 * i;
+            l[i] = e < bb ? e / b : 0;
+            q[i] = e < bb ? e % b : 0;
+            cur[i] = W[src_row(base + l[i]) * sb + base + q[i]] * inv_lambda + (l[i] == q[i] ? mdbl : 0.0);
+            if (e < bb) sh[e] = cur[i];
+        }
+        wave_lds_sync();
+        bool bad = false;
+        for (int kk = 0; kk < b; ++kk) {
+            const double piv = sh[kk * b + kk];
+            if (!(piv > 0.0) || !isfinite(piv)) bad = true;
+            const double pinv = 1.0 / piv;
+#pragma unroll
+            for (int i = 0; i < EP; ++i) {
+                if (64 * i >= bb) break;
+                rowk[i] = q[i] == kk ? 1.0 : sh[kk * b + q[i]];
+                colk[i] = sh[l[i] * b + kk];
+            }
+            wave_lds_sync();          // all reads come before the writes
+#pragma unroll
+            for (int i = 0; i < EP; ++i) {
+                if (64 * i >= bb) break;
+                const double nk = rowk[i] * pinv;         // new row-kk entry in column q
+                cur[i] = l[i] == kk ? nk : (q[i] == kk ? 0.0 : cur[i]) - nk * colk[i];
+                if (tid + 64 * i < bb) sh[tid + 64 * i] = cur[i];
+            }
+            wave_lds_sync();
+        }
+        if (bad && tid == 0) set_status(status, KDCD_ERR_NOT_SPD);
+#pragma unroll
+        for (int i = 0; i < EP; ++i)
+            if (tid + 64 * i < bb) Dinv[(int64_t)j * bb + tid + 64 * i] = cur[i];
+        return;
+    }
     for (int e = tid; e < bb; e += blockDim.x) {
         const int l = e / b, q = e % b;
         sh[e] = W[src_row(base + l) * sb + base + q] * inv_lambda + (l == q ? mdbl : 0.0);
@@ -303,7 +350,6 @@ __global__ __launch_bounds__(256) void finish_kernel(const FinishDesc d, int32_t
         __syncthreads();
     }
     if (bad && tid == 0) set_status(status, KDCD_ERR_NOT_SPD);
-    double *Dinv = d.Dinv[k];
     for (int e = tid; e < bb; e += blockDim.x) Dinv[(int64_t)j * bb + e] = sh[e];
 }
 
