@@ -93,10 +93,10 @@ __device__ __forceinline__ double wave_sum_xor16_32(double v)
 // ------------------------------------------------------------------ host side
 
 // A workspace for work on the stream (*bytes: what is needed, then what it holds); its
-// return, once the stream has been synchronised; and the release of all returned ones
-// that the library keeps.
+// return, which waits for the stream (the wait's outcome); and the release of all
+// returned ones that the library keeps.
 hipError_t workspace_alloc(void **ptr, size_t *bytes, hipStream_t st);
-void workspace_free(void *ptr, size_t bytes, hipStream_t st);
+hipError_t workspace_free(void *ptr, size_t bytes, hipStream_t st);
 void workspace_trim();
 
 // Kernel timing without marker packets: a profiled solve arms a start / stop

@@ -206,8 +206,7 @@ kdcd_status kdcd_sampler_select(const float *keys, int64_t m, int32_t s, double 
         launch_select(a, st) != hipSuccess ||
         hipMemcpyAsync(&hs, status, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess)
         rc = KDCD_ERR_HIP;
-    if (hipStreamSynchronize(st) != hipSuccess) rc = KDCD_ERR_HIP;
-    workspace_free(ws, bytes, st);
+    if (workspace_free(ws, bytes, st) != hipSuccess) rc = KDCD_ERR_HIP;
     if (rc == KDCD_OK) rc = (kdcd_status)hs;
     return rc;
 }

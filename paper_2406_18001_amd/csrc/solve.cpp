@@ -259,10 +259,7 @@ struct Workspace {
     hipStream_t st = nullptr;
     ~Workspace()
     {
-        if (owned && base) {
-            (void)hipStreamSynchronize(st);
-            workspace_free(base, owned, st);
-        }
+        if (owned && base) (void)workspace_free(base, owned, st);
     }
     template <class T> T *at(size_t off) const { return reinterpret_cast<T *>(base + off); }
 };
@@ -290,8 +287,10 @@ namespace kdcd {
 
 // Freed workspaces, kept for later calls: at most kKeepBlocks and kKeepBytes a device,
 // the oldest go first; kdcd_graph_cache_clear and a failed allocation return them all.  A
-// block comes back only after its call has synchronised its stream, so it is idle and
-// any thread and stream may take it.  Allocated and freed by each call, a workspace of
+// block comes back only after its stream has been waited for, so it is idle and any
+// thread and stream may take it.  Where the wait fails, and on a stream under capture
+// (its memory is the graph's), a call's block is neither taken from the kept ones nor
+// kept.  Allocated and freed by each call, a workspace of
 // up to 64 MB cost 40 us a call and a larger one 300.
 namespace {
 constexpr int kKeepDevices = 64;
@@ -314,12 +313,21 @@ int stream_device(hipStream_t st)
     }
     return dev < kKeepDevices ? dev : -1;
 }
+// Whether work on the stream is recorded into a graph (or the runtime does not say).
+bool stream_records(hipStream_t st)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
 }  // namespace
 
 hipError_t workspace_alloc(void **ptr, size_t *bytes, hipStream_t st)
 {
-    const int dev = stream_device(st);
     const size_t need = *bytes;
+    if (stream_records(st)) return hipMallocAsync(ptr, need, st);
+    const int dev = stream_device(st);
     if (dev >= 0) {
         Kept &k = kept();
         std::lock_guard<std::mutex> lk(k.mu);
@@ -347,11 +355,16 @@ hipError_t workspace_alloc(void **ptr, size_t *bytes, hipStream_t st)
     return hipMallocAsync(ptr, need, st);
 }
 
-void workspace_free(void *ptr, size_t bytes, hipStream_t st)
+hipError_t workspace_free(void *ptr, size_t bytes, hipStream_t st)
 {
+    if (stream_records(st)) {
+        (void)hipFreeAsync(ptr, st);
+        return hipStreamSynchronize(st);
+    }
+    const hipError_t idle = hipStreamSynchronize(st);
     const int dev = stream_device(st);
     std::vector<void *> drop;
-    if (dev < 0 || bytes > kKeepBytes) {
+    if (idle != hipSuccess || dev < 0 || bytes > kKeepBytes) {
         drop.push_back(ptr);
     } else {
         Kept &k = kept();
@@ -368,6 +381,7 @@ void workspace_free(void *ptr, size_t bytes, hipStream_t st)
     }
     for (void *p : drop) (void)hipFreeAsync(p, st);
     if (!drop.empty()) (void)hipStreamSynchronize(st);
+    return idle;
 }
 
 void workspace_trim()
