@@ -98,6 +98,8 @@ __device__ __forceinline__ double wave_sum_xor16_32(double v)
 hipError_t workspace_alloc(void **ptr, size_t *bytes, hipStream_t st);
 hipError_t workspace_free(void *ptr, size_t bytes, hipStream_t st);
 void workspace_trim();
+// hipMalloc, with the kept ones released where they are in the way.
+hipError_t device_alloc(void **ptr, size_t bytes);
 
 // Kernel timing without marker packets: a profiled solve arms a start / stop
 // event pair for the calling thread, and the next kernel started through

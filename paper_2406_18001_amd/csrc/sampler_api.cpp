@@ -39,11 +39,10 @@ kdcd_status kdcd_sampler_create(kdcd_sampler **out, uint64_t seed)
         return KDCD_ERR_HIP;
     }
     const size_t np = sizeof(float) * SMP_NP;
-    bool ok = hipMalloc(&m->params, np) == hipSuccess && hipMalloc(&m->mom, np) == hipSuccess &&
-              hipMalloc(&m->vel, np) == hipSuccess &&
-              hipMalloc(&m->gpart, np * (size_t)kMaxTrainBlocks) == hipSuccess &&
-              hipMalloc(&m->lpart, sizeof(float) * kMaxTrainBlocks) == hipSuccess &&
-              hipMalloc(&m->lacc, sizeof(double)) == hipSuccess;
+    auto get = [](auto **p, size_t bytes) { return device_alloc(reinterpret_cast<void **>(p), bytes) == hipSuccess; };
+    bool ok = get(&m->params, np) && get(&m->mom, np) && get(&m->vel, np) &&
+              get(&m->gpart, np * (size_t)kMaxTrainBlocks) && get(&m->lpart, sizeof(float) * kMaxTrainBlocks) &&
+              get(&m->lacc, sizeof(double));
     if (!ok) {
         kdcd_sampler_destroy(m);
         return KDCD_ERR_ALLOC;

@@ -281,6 +281,15 @@ kdcd_status acquire(Workspace &ws, const Layout &L, const kdcd_options *opt, hip
     return KDCD_OK;
 }
 
+// In the layout L or, where the device has not the memory for it, in the least one.
+kdcd_status acquire(Workspace &ws, Layout &L, const Layout &least, const kdcd_options *opt, hipStream_t st)
+{
+    const kdcd_status rc = acquire(ws, L, opt, st);
+    if (rc != KDCD_ERR_ALLOC || L.total <= least.total) return rc;
+    L = least;
+    return acquire(ws, L, opt, st);
+}
+
 }  // namespace
 
 namespace kdcd {
@@ -352,7 +361,20 @@ hipError_t workspace_alloc(void **ptr, size_t *bytes, hipStream_t st)
     (void)hipGetLastError();
     workspace_trim();
     *bytes = need;
-    return hipMallocAsync(ptr, need, st);
+    e = hipMallocAsync(ptr, need, st);
+    if (e != hipSuccess) (void)hipGetLastError();   // (the caller may do with less)
+    return e;
+}
+
+hipError_t device_alloc(void **ptr, size_t bytes)
+{
+    hipError_t e = hipMalloc(ptr, bytes);
+    if (e == hipSuccess && *ptr) return e;
+    (void)hipGetLastError();
+    workspace_trim();
+    e = hipMalloc(ptr, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
 }
 
 hipError_t workspace_free(void *ptr, size_t bytes, hipStream_t st)
@@ -1367,6 +1389,7 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
 
 struct GraphEntry {
     std::string key;
+    size_t bytes = 0;
     int device = -1;
     hipGraphExec_t exec = nullptr;
     char *ws = nullptr;
@@ -1414,7 +1437,8 @@ struct KeyBuilder {
 };
 
 // The cache entry of `key` on the current device, captured and instantiated
-// on first use (with c.mu held): prepare(base) is synchronous set-up before
+// on first use (with c.mu held; the same call in a workspace of another size is another
+// entry): prepare(base) is synchronous set-up before
 // the capture (host-to-device copies of data the graph reads); enqueue(base,
 // stream) is the work to capture.
 GraphEntry *graph_entry(GraphCache &c, const std::string &key, size_t bytes,
@@ -1430,7 +1454,7 @@ GraphEntry *graph_entry(GraphCache &c, const std::string &key, size_t bytes,
         return nullptr;
     }
     for (auto &x : c.entries)
-        if (x.device == dev && x.key == key) {
+        if (x.device == dev && x.bytes == bytes && x.key == key) {
             x.used = ++c.tick;
             return &x;
         }
@@ -1441,6 +1465,7 @@ GraphEntry *graph_entry(GraphCache &c, const std::string &key, size_t bytes,
     }
     GraphEntry ne;
     ne.key = key;
+    ne.bytes = bytes;
     ne.device = dev;
     if (opt.workspace) {
         if (opt.workspace_bytes < bytes) rc = KDCD_ERR_WORKSPACE;
@@ -1449,7 +1474,7 @@ GraphEntry *graph_entry(GraphCache &c, const std::string &key, size_t bytes,
         if (rc != KDCD_OK) return nullptr;
     } else {
         void *p = nullptr;
-        if (hipMalloc(&p, bytes) != hipSuccess || !p) {
+        if (device_alloc(&p, bytes) != hipSuccess || !p) {
             rc = KDCD_ERR_ALLOC;
             return nullptr;
         }
@@ -1681,14 +1706,15 @@ kdcd_status run_persist(const SolveArgs &sa, const Layout &L, char *base, size_t
     return rc;
 }
 
-kdcd_status run_solve(const SolveArgs &sa)
+// The layout of a solve, with the memory that only makes it faster (full) or without.
+Layout solve_layout(const SolveArgs &sa, bool full)
 {
-    kdcd_status rc = check_monitor(sa.A, sa.opt);
-    if (rc != KDCD_OK) return rc;
     Layout L = make_layout(sa.problem, sa.A, sa.kernel, sa.b, sa.s, sa.opt.compute);
-    grow_panel(L, sa.A, &sa.opt);
-    // (the lookahead loop's Gram launches take the rows of two blocks)
-    grow_gram(L, (int64_t)sa.s * sa.b, L.la_ok ? 2 : 1, (sa.H + sa.s - 1) / sa.s, sa.opt);
+    if (full) {
+        grow_panel(L, sa.A, &sa.opt);
+        // (the lookahead loop's Gram launches take the rows of two blocks)
+        grow_gram(L, (int64_t)sa.s * sa.b, L.la_ok ? 2 : 1, (sa.H + sa.s - 1) / sa.s, sa.opt);
+    }
     if (sa.opt.monitor_every > 0) {
         add_monitor(L, sa.A->m, (int64_t)sa.s * sa.b);
         // the lookahead loop keeps two stored kernel blocks (not in a caller's
@@ -1698,27 +1724,43 @@ kdcd_status run_solve(const SolveArgs &sa)
             L.total += align256(sizeof(double) * (size_t)((int64_t)sa.s * sa.b * sa.A->m));
         }
     }
+    return L;
+}
+
+kdcd_status run_solve_graph(const SolveArgs &sa, const Layout &L)
+{
+    const kdcd_status rc = run_graph_windowed(sa, L);
+    if (rc != KDCD_ERR_UNSUPPORTED) return rc;
+    KeyBuilder kb;
+    kb.add('S');
+    kb.add(sa.problem);
+    kb.matrix(sa.A);
+    kb.add(sa.y);
+    kb.kernel(sa.kernel);
+    kb.add(sa.C); kb.add(sa.lambda); kb.add(sa.b); kb.add(sa.s); kb.add(sa.H);
+    kb.add(sa.idx); kb.add(sa.alpha);
+    kb.options(sa.opt);
+    return run_graph(kb.k, L.total, sa.opt, sa.st, nullptr,
+                     [&](char *base, hipStream_t cs) {
+                         SolveArgs g = sa;
+                         g.st = cs;
+                         StageTimer off;
+                         return enqueue_solve(g, L, base, off);
+                     });
+}
+
+kdcd_status run_solve(const SolveArgs &sa)
+{
+    kdcd_status rc = check_monitor(sa.A, sa.opt);
+    if (rc != KDCD_OK) return rc;
+    const Layout least = solve_layout(sa, false);
+    Layout L = solve_layout(sa, true);
     if (sa.opt.flags & KDCD_FLAG_GRAPH) {
-        rc = run_graph_windowed(sa, L);
-        if (rc != KDCD_ERR_UNSUPPORTED) return rc;
-        KeyBuilder kb;
-        kb.add('S');
-        kb.add(sa.problem);
-        kb.matrix(sa.A);
-        kb.add(sa.y);
-        kb.kernel(sa.kernel);
-        kb.add(sa.C); kb.add(sa.lambda); kb.add(sa.b); kb.add(sa.s); kb.add(sa.H);
-        kb.add(sa.idx); kb.add(sa.alpha);
-        kb.options(sa.opt);
-        return run_graph(kb.k, L.total, sa.opt, sa.st, nullptr,
-                         [&](char *base, hipStream_t cs) {
-                             SolveArgs g = sa;
-                             g.st = cs;
-                             StageTimer off;
-                             return enqueue_solve(g, L, base, off);
-                         });
+        rc = run_solve_graph(sa, L);
+        // (the one allocation comes before any work)
+        return rc == KDCD_ERR_ALLOC && L.total > least.total ? run_solve_graph(sa, least) : rc;
     }
-    const int64_t persist = persist_groups(sa);
+    int64_t persist = persist_groups(sa);
     size_t o_save = 0, o_slots = 0;
     if (persist > 0) {
         o_save = L.total;
@@ -1726,7 +1768,8 @@ kdcd_status run_solve(const SolveArgs &sa)
         L.total = o_slots + align256(sizeof(uint64_t) * (size_t)(3 * persist * sa.s));
     }
     Workspace ws;
-    if ((rc = acquire(ws, L, &sa.opt, sa.st)) != KDCD_OK) return rc;
+    if ((rc = acquire(ws, L, least, &sa.opt, sa.st)) != KDCD_OK) return rc;
+    if (L.total < o_slots) persist = 0;
     if (persist > 0) {
         bool done = false;
         rc = run_persist(sa, L, ws.base, o_save, o_slots, persist, &done);
@@ -2504,10 +2547,11 @@ kdcd_status kdcd_kernel_rhs(const kdcd_matrix *A, const kdcd_kernel *kernel, con
     if (!S || !beta || !r || sb < 1) return KDCD_ERR_INVALID_ARG;
     if (sb > kMaxSB) return KDCD_ERR_UNSUPPORTED;
     const hipStream_t st = (hipStream_t)stream;
-    Layout L = make_layout(0, A, kernel, 1, sb, compute);
+    const Layout least = make_layout(0, A, kernel, 1, sb, compute);
+    Layout L = least;
     grow_panel(L, A, nullptr);
     Workspace ws;
-    if ((rc = acquire(ws, L, nullptr, st)) != KDCD_OK) return rc;
+    if ((rc = acquire(ws, L, least, nullptr, st)) != KDCD_OK) return rc;
     int32_t *status = ws.at<int32_t>(L.status);
     double *norms = ws.at<double>(L.norms);
     double *partial = ws.at<double>(L.partial);
@@ -2558,10 +2602,11 @@ static kdcd_status kernel_matvec(const kdcd_matrix *A, const kdcd_kernel *kernel
 {
     const int64_t m = A->m;
     const int32_t chunk = kMaxSB;
-    Layout L = make_layout(2, A, kernel, 1, chunk, KDCD_F64);
+    const Layout least = make_layout(2, A, kernel, 1, chunk, KDCD_F64);
+    Layout L = least;
     grow_panel(L, A, nullptr);
     Workspace ws;
-    kdcd_status rc = acquire(ws, L, nullptr, st);
+    kdcd_status rc = acquire(ws, L, least, nullptr, st);
     if (rc != KDCD_OK) return rc;
     int32_t *status = ws.at<int32_t>(L.status);
     double *norms = ws.at<double>(L.norms);
@@ -2632,7 +2677,7 @@ kdcd_status kdcd_ksvm_eval(const kdcd_matrix *A, const double *y, const kdcd_ker
     std::vector<double> beta((size_t)A->m);
     for (int64_t p = 0; p < A->m; ++p) beta[p] = hy[p] * ha[p];
     double *dbeta = nullptr;
-    if (hipMalloc(&dbeta, sizeof(double) * (size_t)A->m) != hipSuccess) return KDCD_ERR_ALLOC;
+    if (device_alloc(reinterpret_cast<void **>(&dbeta), sizeof(double) * (size_t)A->m) != hipSuccess) return KDCD_ERR_ALLOC;
     (void)hipMemcpy(dbeta, beta.data(), sizeof(double) * (size_t)A->m, hipMemcpyHostToDevice);
     std::vector<double> Kb;
     rc = kernel_matvec(A, kernel, dbeta, &Kb, nullptr, st);

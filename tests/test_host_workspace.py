@@ -57,3 +57,55 @@ assert solve(A, 4, 16, 64) == -7 and get("mallocs") == 1
 put("sync_error", 0)
 assert solve(A, 4, 16, 64) == 0 and get("mallocs") == 2
 """)
+
+
+# calls whose own workspace holds more than they need: Grams ahead, the full CSR panel
+# (graphs too), the exchange words of the one-launch solve
+CALLS = {
+    "gram": ("A = dense(3000, 64)", "solve(A, 8, 64, 64 * 20, compute=BF16X3, flags=F, alpha=a)", "1, *W(A), 8, 64, BF16X3"),
+    "panel": ("A = csr(2000, 100000, 400000)", "solve(A, 1, 64, 64 * 20, 'svm', flags=F, alpha=a)", "0, *W(A), 1, 64, F64"),
+    "one_launch": ("A = dense(7000, 64)", "solve(A, 1, 32, 32 * 20, 'svm', flags=F, alpha=a)", "0, *W(A), 1, 32, F64"),
+}
+SETUP = """
+a = (f64 * 200000)()
+W = lambda A: (ctypes.byref(A), ctypes.byref(RBF))
+F = %d
+%s
+need = lib.kdcd_workspace_bytes(%s)
+"""
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+@pytest.mark.parametrize("name", CALLS)
+def test_least_memory_will_do(host, name, graph):
+    A, call, ws = CALLS[name]
+    host(SETUP % (graph, A, ws) + f"""
+put("memory", need + (64 << 10), size)          # (64 KiB: a graph's window of indices)
+assert {call} == 0 and {call} == 0
+assert get("largest", size) <= need + (64 << 10)
+put("memory", 1 << 40, size)
+stub.stub_forget()
+assert {call} == 0                              # and with the memory, all of it
+assert get("largest", size) >= need + (80 << 10) or {graph and name == "one_launch"}
+""")
+
+
+def test_least_memory_of_a_product(host):
+    host("""
+A = csr(2000, 100000, 400000)
+need = lib.kdcd_workspace_bytes(0, ctypes.byref(A), ctypes.byref(RBF), 1, 64, F64)
+put("memory", need + 4096, size)
+r = (f64 * 64)()
+assert lib.kdcd_kernel_rhs(ctypes.byref(A), ctypes.byref(RBF), 4096, 64, 4096, None, r, None, F64, None) == 0
+""")
+
+
+@pytest.mark.parametrize("call", ["solve(B, 4, 16, 16 * 40, flags=GRAPH)", "lib.kdcd_sampler_create(ctypes.byref(P()), ctypes.c_uint64(1))"])
+def test_kept_memory_makes_way(host, call):
+    """Memory that is only kept does not fail an allocation."""
+    host(f"""
+A, B = dense(2000000, 40), dense(3000, 40)
+assert solve(A, 4, 16, 64) == 0
+put("memory", get("held", size) + 4096, size)
+assert {call} == 0
+""")
