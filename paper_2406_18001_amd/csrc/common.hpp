@@ -187,6 +187,9 @@ struct KBlockArgs {
     // launch_csr_panel_init); null keeps the broadcast kernel
     void *csr_panel = nullptr;
     size_t csr_panel_bytes = 0;
+    // CSR: sampled rows of a whole index block of the solve, which with A and the panel
+    // memory decides the kernels of all its launches (0: sb)
+    int32_t csr_sb = 0;
     // CSR: the longest row of A (stored entries) when the caller knows it, else
     // -1; a chunk of sampled rows that cannot exceed the panel then skips the
     // broadcast launch that would only run for an overflowing chunk
@@ -258,7 +261,7 @@ void tune_store(int32_t compute, int64_t n, int32_t sb, int id);   // id < 0 rem
 // workspace allocated by the call holds (room for wide chunks of long rows).
 size_t csr_panel_min_bytes(int64_t n);
 size_t csr_panel_full_bytes(const kdcd_matrix *A);
-hipError_t launch_csr_panel_init(const kdcd_matrix *A, void *panel, hipStream_t st);
+hipError_t launch_csr_panel_init(const KBlockArgs &a, hipStream_t st);   // (a.sb is not looked at if a.csr_sb is set)
 int64_t kblock_mixed_row_groups(int cfg, int64_t m, int64_t n, int32_t sb, int32_t compute,
                                 bool batch);
 // Tile configurations of the batched products, tuned under compute + KDCD_TUNE_BATCH.

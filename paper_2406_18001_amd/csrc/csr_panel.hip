@@ -29,7 +29,7 @@
 // 50000 x 50000 with rows of 100 entries an outer iteration with 1 / 16 / 32 / 64
 // sampled rows takes 58 / 72 / 100 / 156 us against 40 / 102 / 81 / 149 with the
 // broadcast and dense-head kernels; with rows of 130, 70 / 87 / 128 / 198 against
-// 85 / 132 / 524 / 1024.
+// 85 / 132 / 524 / 1024.  From there on csr_takes_panel (kblock_csr.hip) decides.
 //
 // Ids are handed out by an atomic counter and differ from run to run, but a
 // row's sum only depends on its own entries' order: hit i of a row goes to lane
@@ -529,7 +529,7 @@ size_t csr_dense_panel_full_bytes(const kdcd_matrix *A)
 CsrPanelPlan csr_panel_plan(const KBlockArgs &a)
 {
     const kdcd_matrix *A = a.A;
-    CsrPanelPlan p{0, 0, false};
+    CsrPanelPlan p{0, 0, false, false};
     const size_t fixed = pp_fixed_bytes(A->n);
     if (!a.csr_panel || a.csr_panel_bytes <= fixed || A->m > INT32_MAX || A->nnz <= 0) return p;
     const int64_t room = (int64_t)((a.csr_panel_bytes - fixed) / sizeof(double));
@@ -546,6 +546,7 @@ CsrPanelPlan csr_panel_plan(const KBlockArgs &a)
             p.lpr = lpr;
             p.cap = (uint32_t)cap;
             p.sure = sure;
+            p.fits = sure || likely;
             return p;
         }
     }

@@ -7,12 +7,13 @@ namespace kdcd {
 
 // Chunks of lpr sampled rows against a panel of cap rows (lpr 0: no panel).
 // sure: no chunk can have more than cap distinct columns; otherwise every
-// chunk's product is followed by the broadcast kernel, gated on the build's
-// overflow flag.
+// chunk's product is followed by a kernel that needs no panel, gated on the
+// build's overflow flag.  fits: chunks of average rows have not.
 struct CsrPanelPlan {
     int lpr;
     uint32_t cap;
     bool sure;
+    bool fits;
 };
 bool csr_long_rows(const kdcd_matrix *A);                   // rows long enough for this path
 CsrPanelPlan csr_panel_plan(const KBlockArgs &a);

@@ -38,6 +38,7 @@ constexpr int CSR_VMAX = 3072;        // stored entries of one chunk of sampled 
 static_assert(CSR_VMAX <= 32767, "value offsets are 16-bit");
 constexpr int CSR_HS = 4096;          // hash slots (power of two, > CSR_VMAX)
 constexpr int CSR_MAXGROUPS = 512;    // row groups of the U-part
+constexpr double kCsrWaveMinAvg = 128.0;   // average row length from which rows get a wave each
 
 __device__ __forceinline__ int64_t clampi(int64_t v, int64_t lo, int64_t hi)
 {
@@ -445,6 +446,155 @@ __global__ __launch_bounds__(CSR_NT) __attribute__((amdgpu_waves_per_eu(RPW > 1 
     }
 }
 
+// Long rows (chunks of at most WJ = 8 sampled rows): one wave walks one data
+// row, 64 stored entries at a time (coalesced loads), each lane keeping its
+// own partial sums for the chunk's sampled rows; the lanes' sums meet in a
+// fixed xor tree at the end of the row, so the result is deterministic.
+constexpr int WJ = 8;
+
+template <int KIND>
+__global__ __launch_bounds__(CSR_NT) __attribute__((amdgpu_waves_per_eu(4))) void kblock_csr_wave_kernel(
+    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx,
+    const double *__restrict__ val, int64_t m, int64_t nnz, const int32_t *__restrict__ S,
+    int32_t sb, const double *__restrict__ norms, KParams kp, const double *__restrict__ beta,
+    const double *__restrict__ bscale, double *__restrict__ partial, double *__restrict__ W,
+    int32_t n_row_groups, double *__restrict__ carry, int32_t *status, int32_t jbeg,
+    int32_t jend, const int32_t *__restrict__ gate, double *__restrict__ U)
+{
+    constexpr int NW = CSR_NT / 64;
+    constexpr int NB = KIND == KDCD_KERNEL_RBF ? 2 : 4;   // entries per lane per batch
+    using MaskT = uint32_t;
+    __shared__ int32_t hkey[CSR_HS];
+    __shared__ MaskT hmask[CSR_HS];
+    __shared__ int16_t hbase[CSR_HS];      // value offsets (< CSR_VMAX)
+    __shared__ uint32_t hfilt[CSR_FBITS / 32];
+    __shared__ double hval[CSR_VMAX];
+    __shared__ int32_t rowoff[WJ + 1];
+    __shared__ int32_t scan[CSR_NT];
+    __shared__ double red[NW][WJ];
+
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const bool is_w = (int)blockIdx.x >= n_row_groups;
+    if (is_w && W == nullptr) return;
+    const int wblk = (int)blockIdx.x - n_row_groups;   // W-part: sampled rows [wblk*NW, +NW)
+    auto rp = [&](int64_t r) { return clampi(row_ptr[clampi(r, 0, m)], 0, nnz); };
+
+    if (gate && *gate == 0) return;
+    for (int j0 = jbeg; j0 < jend;) {
+        int j1 = build_panel<MaskT, WJ>(j0, -1, row_ptr, col_idx, val, m, nnz, S, jend, hkey, hfilt,
+                                        hmask, hbase, hval, rowoff, scan, status);
+        int npieces = 1;
+        if (j1 == -2) {                  // a sampled row longer than the panel: in pieces
+            if (!carry) {
+                if (tid == 0) set_status(status, KDCD_ERR_UNSUPPORTED);
+                return;
+            }
+            const int64_t r = clampi(S[j0], 0, m - 1);
+            npieces = (int)((rp(r + 1) - rp(r) + CSR_VMAX - 1) / CSR_VMAX);
+            j1 = j0 + 1;
+        }
+        const int nj = j1 - j0;
+        // lane j < nj owns sampled row j0 + j for the map and the reduction
+        const bool jok = lane < nj;
+        const int64_t Sj = clampi(S[j0 + (jok ? lane : 0)], 0, m - 1);
+        const double nbj = (KIND == KDCD_KERNEL_RBF) ? norms[Sj] : 0.0;
+        double colsum = 0.0;
+        for (int pc = 0; pc < npieces; ++pc) {
+        if (npieces > 1) {               // dot products summed over the pieces in carry[]
+            __syncthreads();
+            build_panel<MaskT, WJ>(j0, pc, row_ptr, col_idx, val, m, nnz, S, jend, hkey, hfilt, hmask,
+                                   hbase, hval, rowoff, scan, status);
+        }
+        const bool last = pc + 1 == npieces;
+        const int64_t r_first = is_w ? (int64_t)wblk * NW + wid : (int64_t)blockIdx.x * NW + wid;
+        const int64_t r_end = is_w ? min((int64_t)sb, (int64_t)(wblk + 1) * NW) : m;
+        const int64_t r_step = is_w ? NW : (int64_t)n_row_groups * NW;
+        for (int64_t rix = r_first; rix < r_end; rix += r_step) {
+            const int64_t row = is_w ? clampi(S[rix], 0, m - 1) : rix;
+            const int64_t e_beg = rp(row), len = rp(row + 1) - e_beg;
+            double acc[WJ];
+#pragma unroll
+            for (int j = 0; j < WJ; ++j) acc[j] = 0.0;
+            int32_t cb[NB], nc[NB];
+            double vb[NB], nv[NB];
+            auto load_batch = [&](int64_t eb, int32_t (&c)[NB], double (&v)[NB]) {
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    const int64_t off = eb + (int64_t)u * 64 + lane;
+                    const int64_t ec = clampi(e_beg + off, 0, nnz - 1);
+                    const bool ok = off < len;
+                    c[u] = ok ? col_idx[ec] : -1;
+                    v[u] = ok ? val[ec] : 0.0;
+                }
+            };
+            constexpr int64_t STEP = (int64_t)NB * 64;
+            if (len > 0) load_batch(0, cb, vb);
+            for (int64_t eb = 0; eb < len; eb += STEP) {
+                if (eb + STEP < len) load_batch(eb + STEP, nc, nv);
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    if (cb[u] >= 0) {
+                        const int h = hash_find(hkey, hfilt, cb[u]);
+                        if (h >= 0) {
+                            const MaskT msk = hmask[h];
+                            const int bs = hbase[h];
+                            const double a = vb[u];
+#pragma unroll
+                            for (int j = 0; j < WJ; ++j)
+                                if ((msk >> j) & 1u)
+                                    acc[j] += a * hval[bs + popc((MaskT)(msk & ((1u << j) - 1u)))];
+                        }
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    cb[u] = nc[u];
+                    vb[u] = nv[u];
+                }
+            }
+            double mine = 0.0;
+#pragma unroll
+            for (int j = 0; j < WJ; ++j) {
+                double v = acc[j];
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+                if (lane == j) mine = v;
+            }
+            if (jok) {
+                if (npieces > 1) {
+                    const int64_t ci = is_w ? m + rix : row;
+                    if (pc > 0) mine += carry[ci];
+                    if (!last) carry[ci] = mine;
+                }
+                if (last) {
+                    const double na = (KIND == KDCD_KERNEL_RBF) ? norms[row] : 0.0;
+                    const double kv = kernel_map<KIND>(mine, na, nbj, row == Sj, kp);
+                    if (is_w) {
+                        W[rix * sb + j0 + lane] = kv;
+                    } else {
+                        double bv = beta[row];
+                        if (bscale) bv *= bscale[row];
+                        colsum += bv * kv;
+                        if (U) U[(int64_t)(j0 + lane) * m + row] = kv;
+                    }
+                }
+            }
+        }
+        }   // pieces
+        if (!is_w) {
+            if (lane < WJ) red[wid][lane] = colsum;
+            __syncthreads();
+            if (tid < nj) {
+                double t = 0.0;
+                for (int w = 0; w < NW; ++w) t += red[w][tid];
+                partial[(int64_t)blockIdx.x * sb + j0 + tid] = t;
+            }
+        }
+        __syncthreads();
+        j0 = j1;
+    }
+}
+
 // ---------------------------------------------------------------- dense head
 // Chunks of up to 32 sampled rows, short data rows.  The panel's most shared
 // columns -- those stored by at least t* of the chunk's sampled rows, t* the
@@ -728,16 +878,53 @@ int csr_rows_per_wave(const kdcd_matrix *A, int32_t sb)
     return 64 / lpr;
 }
 
-// Kernel choice by the average row length (a property of A alone, so that one
-// panel memory serves every launch of a solve): long rows -> the dense-panel
-// product; short rows -> the dense-head kernel (more than 16 sampled rows) or
-// the broadcast / scatter kernel.
-enum CsrPath { CSR_BROADCAST, CSR_PANEL, CSR_HEAD };
+// Whether the launches of a solve take the dense-panel product: one answer for all of
+// them (A, the whole index block, the panel memory), which the panel memory is laid out
+// for.  Long rows take it but for
+//   - a panel too small for the columns of eight average rows: every chunk would overflow
+//     (a caller's workspace, 30000 x 500, rows of 250, 64 sampled: 2070 us an outer
+//     iteration with the gated kernel doing all the work, 580 with the wave kernel);
+//   - a panel for fewer rows than a dense-head chunk that holds the block's: more passes
+//     (60000 x 20000, rows of 113, 32 sampled: four passes 226, dense head 90);
+//   - rows of even length (no long ones to balance, which is half of what it saves) where
+//     the other kernels have one pass and the code words cost more than it: a block of
+//     one dense-head chunk (20000 x 2000, rows of 113, 24 sampled: 68 / 44); few
+//     sampled rows, and rows too short for the wave kernel (60000 x 10^6, rows of 113, 1
+//     sampled: 73 / 41) or code words that no cache holds (20000 x 10^6, rows of 1000, 1
+//     sampled: 151 / 90).
+// Uneven rows (lognormal lengths, Zipf columns): 20000 x 100000, mean 120, 1 / 24 / 64
+// sampled: 44 / 79 / 116 with the panel, 133 / 177 / 555 without; 19996 x 1355191, mean 455,
+// 1 / 4: 107 / 117, 118 / 184.
+constexpr int64_t kCodeInCache = 1 << 17;    // columns
+bool csr_takes_panel(const KBlockArgs &a)
+{
+    const kdcd_matrix *A = a.A;
+    if (!csr_long_rows(A)) return false;
+    KBlockArgs whole = a;
+    if (a.csr_sb > 0) whole.sb = a.csr_sb;
+    const CsrPanelPlan p = csr_panel_plan(whole);
+    if (!p.lpr || !p.fits) return false;
+    const int32_t sb = whole.sb;
+    const double avg = (double)A->nnz / (double)A->m;
+    // (rows of about average length fill nine tenths of a dense-head chunk)
+    const bool head = sb > 16 && avg * std::min(sb, HD_NJ) <= 0.9 * HD_CAP;
+    if (head && p.lpr < HD_NJ) return false;
+    if (a.csr_max_row < 0 || (double)a.csr_max_row > 2.0 * avg) return true;    // uneven, or not known
+    if (head) return sb > HD_NJ;
+    if (sb <= 8 && avg < kCsrWaveMinAvg) return false;
+    return !(sb <= 4 && avg * sb <= CSR_VMAX && A->n > kCodeInCache);
+}
+
+// Kernel choice.  Long rows take the dense-panel product where csr_takes_panel says so;
+// otherwise long rows in chunks of <= 8 sampled rows take one wave per row, more than 16
+// sampled rows the dense-head kernel, the rest the broadcast / scatter kernel.
+enum CsrPath { CSR_BROADCAST, CSR_WAVE, CSR_PANEL, CSR_HEAD };
 CsrPath csr_path(const KBlockArgs &a)
 {
     const kdcd_matrix *A = a.A;
-    if (csr_long_rows(A) && csr_panel_plan(a).lpr) return CSR_PANEL;
-    return a.sb > 16 && a.csr_panel && !csr_long_rows(A) ? CSR_HEAD : CSR_BROADCAST;
+    if (csr_takes_panel(a)) return CSR_PANEL;
+    if (csr_rows_per_wave(A, a.sb) == 8 && (double)A->nnz >= kCsrWaveMinAvg * (double)A->m) return CSR_WAVE;
+    return a.sb > 16 && a.csr_panel ? CSR_HEAD : CSR_BROADCAST;
 }
 
 bool csr_takes_head(const KBlockArgs &a) { return csr_path(a) == CSR_HEAD; }
@@ -767,12 +954,13 @@ size_t csr_panel_full_bytes(const kdcd_matrix *A)
                             : csr_panel_min_bytes(A->n);
 }
 
-hipError_t launch_csr_panel_init(const kdcd_matrix *A, void *panel, hipStream_t st)
+hipError_t launch_csr_panel_init(const KBlockArgs &a, hipStream_t st)
 {
-    if (csr_long_rows(A)) return launch_csr_dense_panel_init(A, panel, st);
+    const kdcd_matrix *A = a.A;
+    if (csr_takes_panel(a)) return launch_csr_dense_panel_init(A, a.csr_panel, st);
     const int64_t blocks = std::min<int64_t>((A->n + 255) / 256, 4096);
     hipLaunchKernelGGL(csr_panel_init_kernel, dim3((unsigned)std::max<int64_t>(blocks, 1)), dim3(256),
-                       0, st, panel, A->n);
+                       0, st, a.csr_panel, A->n);
     return hipGetLastError();
 }
 
@@ -839,22 +1027,32 @@ hipError_t launch_kblock_csr(const KBlockArgs &a, hipStream_t st)
         }
         return hipGetLastError();
     }
-    const int64_t rows_per_wg = (CSR_NT / 64) * rpw;
+    // the kernels that need no panel, on sampled rows [jbeg, jend); long rows: one wave
+    // per data row
+    const bool wave = rpw == 8 && (double)A->nnz >= kCsrWaveMinAvg * (double)A->m;
+    const int64_t rows_per_wg = (CSR_NT / 64) * (wave ? 1 : rpw);
     const int64_t n_w = a.W ? (a.sb + rows_per_wg - 1) / rows_per_wg : 0;
-    // the broadcast kernel on sampled rows [jbeg, jend)
     auto broadcast = [&](int64_t groups, int32_t jbeg, int32_t jend, const int32_t *gate) {
         dim3 grid((unsigned)(groups + n_w)), block(CSR_NT);
-#define KDCD_CSR(RPW, KIND)                                                                   \
-    KDCD_TIMED_LAUNCH((kblock_csr_kernel<RPW, KIND>), grid, block, 0, st, A->row_ptr,          \
+#define KDCD_CSR(...)                                                                         \
+    KDCD_TIMED_LAUNCH((__VA_ARGS__), grid, block, 0, st, A->row_ptr,                           \
                        A->col_idx, A->values, A->m, A->nnz, a.S, a.sb, a.norms, a.kp, a.beta,  \
                        a.beta_scale, a.partial, a.W, (int32_t)groups, a.carry, a.status, jbeg, \
                        jend, gate, a.U)
 #define KDCD_CSR_KIND(RPW)                                                                    \
     switch (a.kp.kind) {                                                                      \
-    case KDCD_KERNEL_LINEAR: KDCD_CSR(RPW, KDCD_KERNEL_LINEAR); break;                        \
-    case KDCD_KERNEL_POLY: KDCD_CSR(RPW, KDCD_KERNEL_POLY); break;                            \
-    default: KDCD_CSR(RPW, KDCD_KERNEL_RBF); break;                                           \
+    case KDCD_KERNEL_LINEAR: KDCD_CSR(kblock_csr_kernel<RPW, KDCD_KERNEL_LINEAR>); break;     \
+    case KDCD_KERNEL_POLY: KDCD_CSR(kblock_csr_kernel<RPW, KDCD_KERNEL_POLY>); break;         \
+    default: KDCD_CSR(kblock_csr_kernel<RPW, KDCD_KERNEL_RBF>); break;                        \
     }
+        if (wave) {
+            switch (a.kp.kind) {
+            case KDCD_KERNEL_LINEAR: KDCD_CSR(kblock_csr_wave_kernel<KDCD_KERNEL_LINEAR>); break;
+            case KDCD_KERNEL_POLY: KDCD_CSR(kblock_csr_wave_kernel<KDCD_KERNEL_POLY>); break;
+            default: KDCD_CSR(kblock_csr_wave_kernel<KDCD_KERNEL_RBF>); break;
+            }
+            return;
+        }
         switch (rpw) {
         case 1: KDCD_CSR_KIND(1) break;
         case 2: KDCD_CSR_KIND(2) break;
@@ -864,7 +1062,7 @@ hipError_t launch_kblock_csr(const KBlockArgs &a, hipStream_t st)
 #undef KDCD_CSR_KIND
 #undef KDCD_CSR
     };
-    if (path == CSR_BROADCAST) {
+    if (path != CSR_PANEL) {
         broadcast(groups_for(A->m), 0, a.sb, nullptr);
         return hipGetLastError();
     }

@@ -1168,7 +1168,8 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
         base.csr_panel = ws.at<void>(L.panel);
         base.csr_panel_bytes = L.panel_bytes;
         base.csr_max_row = sa.csr_max_row;
-        if (R.setup) KDCD_HIP_TRY(launch_csr_panel_init(A, base.csr_panel, st));
+        base.csr_sb = sa.s * sa.b;
+        if (R.setup) KDCD_HIP_TRY(launch_csr_panel_init(base, st));
     }
     KBlockArgs kb;
     rc = prepare_lowp(base, L, ws, st, kb, R.setup);
@@ -2579,7 +2580,7 @@ kdcd_status kdcd_kernel_rhs(const kdcd_matrix *A, const kdcd_kernel *kernel, con
         base.carry = ws.at<double>(L.carry);
         base.csr_panel = ws.at<void>(L.panel);
         base.csr_panel_bytes = L.panel_bytes;
-        KDCD_HIP_TRY(launch_csr_panel_init(A, base.csr_panel, st));
+        KDCD_HIP_TRY(launch_csr_panel_init(base, st));
     }
     KBlockArgs kb;
     if ((rc = prepare_lowp(base, L, ws, st, kb)) != KDCD_OK) return rc;
@@ -2635,7 +2636,8 @@ static kdcd_status kernel_matvec(const kdcd_matrix *A, const kdcd_kernel *kernel
             a.carry = ws.at<double>(L.carry);
             a.csr_panel = ws.at<void>(L.panel);
             a.csr_panel_bytes = L.panel_bytes;
-            if (c0 == 0) KDCD_HIP_TRY(launch_csr_panel_init(A, a.csr_panel, st));
+            a.csr_sb = chunk;
+            if (c0 == 0) KDCD_HIP_TRY(launch_csr_panel_init(a, st));
         }
         const int64_t groups = bind_config(a);
         KDCD_HIP_TRY(launch_kblock(a, st));

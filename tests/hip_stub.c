@@ -18,6 +18,7 @@ static char launched[1 << 20];
 
 /* set by the test */
 int stub_capturing, stub_sync_error, stub_coop_refused, stub_coop_gives_up;
+uint64_t stub_row_max;                       /* the longest CSR row */
 size_t stub_memory = (size_t)1 << 40;
 /* read by the test */
 int stub_mallocs, stub_captured_mallocs, stub_uses_captured, stub_coop_launches;
@@ -61,6 +62,7 @@ static int launch(const void *f, void **args)
             for (int64_t i = 0; i < c; ++i) p[i] = v;
         }
     }
+    if (strstr(name, "csr_row_max") && !stub_capturing) **(uint64_t **)args[2] = stub_row_max;
     return 0;
 }
 
