@@ -882,8 +882,8 @@ int csr_rows_per_wave(const kdcd_matrix *A, int32_t sb)
 // them (A, the whole index block, the panel memory), which the panel memory is laid out
 // for.  Long rows take it but for
 //   - a panel too small for the columns of eight average rows: every chunk would overflow
-//     (a caller's workspace, 30000 x 500, rows of 250, 64 sampled: 2070 us an outer
-//     iteration with the gated kernel doing all the work, 580 with the wave kernel);
+//     (a caller's workspace, 60000 x 500, rows of 250, 64 sampled: 2821 us an outer
+//     iteration with the gated kernel doing all the work, 988 with the wave kernel);
 //   - a panel for fewer rows than a dense-head chunk that holds the block's: more passes
 //     (60000 x 20000, rows of 113, 32 sampled: four passes 226, dense head 90);
 //   - rows of even length (no long ones to balance, which is half of what it saves) where
