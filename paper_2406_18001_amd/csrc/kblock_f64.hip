@@ -631,7 +631,8 @@ hipError_t launch_tiles(const KBlockArgs &a, hipStream_t st, int nprob = 0)
 
 }  // namespace
 
-// Tile configurations (MFMA blocks per wave; four waves, one above the other).
+// Tile configurations (MFMA blocks per wave; four waves, one above the other).  Saved
+// tuning tables hold the ids: a new tile takes a new one, none changes its tile.
 struct F64Cfg {
     int tm, tn;
 };
@@ -640,18 +641,21 @@ constexpr F64Cfg kF64Cfgs[] = {
     {2, 2},   // 1: 128 x 32
     {1, 4},   // 2: 64 x 64
     {1, 8},   // 3: 64 x 128
-    {1, 2},   // 4: 64 x 32
+    {1, 8},   // 4: 64 x 128 (once with eight waves)
     {2, 4},   // 5: 128 x 64
-    {1, 1},   // 6: 64 x 16
+    {1, 4},   // 6: 64 x 64 (once with fewer registers)
+    {1, 2},   // 7: 64 x 32
+    {1, 1},   // 8: 64 x 16
 };
 constexpr int kF64NumCfgs = sizeof(kF64Cfgs) / sizeof(kF64Cfgs[0]);
 // Those of the batched launch.
 constexpr F64Cfg kF64BatchCfgs[] = {
-    {1, 1},   // 0: 64 x 16
+    {2, 1},   // 0: 128 x 16
     {2, 2},   // 1: 128 x 32
     {1, 4},   // 2: 64 x 64
     {2, 4},   // 3: 128 x 64
     {1, 2},   // 4: 64 x 32
+    {1, 1},   // 5: 64 x 16
 };
 constexpr int kF64BatchNumCfgs = sizeof(kF64BatchCfgs) / sizeof(kF64BatchCfgs[0]);
 
@@ -685,8 +689,8 @@ static int f64_default_id(int64_t m, int32_t sb)
     if (m >= 0 && tiles_of(m, sb, tm, tn) < 512) tm = 1;
     while (m >= 0 && tn > 1 && tiles_of(m, sb, tm, tn) < 512) tn /= 2;
     if (tn == 4) return tm == 2 ? 5 : 2;
-    if (tn == 2) return tm == 2 ? 1 : 4;
-    return tm == 2 ? 0 : 6;
+    if (tn == 2) return tm == 2 ? 1 : 7;
+    return tm == 2 ? 0 : 8;
 }
 
 int f64_config_id(int64_t m, int64_t n, int32_t sb)
@@ -705,7 +709,7 @@ static int f64_batch_default_id(int64_t m, int32_t sb, int32_t nprob)
     int tn = sb <= 16 ? 1 : (sb <= 32 ? 2 : 4);
     if (tn == 4 && nprob <= 20 && (m < 0 || tiles_of(m, sb, 2, 4) >= 256)) return 3;
     while (m >= 0 && tn > 1 && tiles_of(m, sb, 1, tn) < 256) tn /= 2;
-    return tn == 4 ? 2 : (tn == 2 ? 4 : 0);
+    return tn == 4 ? 2 : (tn == 2 ? 4 : 5);
 }
 
 int f64_batch_config_id(int64_t m, int64_t n, int32_t sb, int32_t nprob)
@@ -741,10 +745,11 @@ hipError_t launch_kblock_f64_main(const KBlockArgs &a, hipStream_t st)
     if (a.batch) {
         const int np = a.batch_nprob > 0 ? a.batch_nprob : kMaxProblems;
         switch (a.cfg >= 0 && a.cfg < kF64BatchNumCfgs ? a.cfg : f64_batch_config_id(A->m, A->n, a.sb, kMaxProblems)) {
-        case 0: return launch_tiles<4, 1, 1, true, 3>(a, st, np);
+        case 0: return launch_tiles<4, 2, 1, true, 3>(a, st, np);
         case 1: return launch_tiles<4, 2, 2, true, 2>(a, st, np);
         case 3: return launch_tiles<4, 2, 4, true, 2>(a, st, np);
         case 4: return launch_tiles<4, 1, 2, true, 3>(a, st, np);
+        case 5: return launch_tiles<4, 1, 1, true, 3>(a, st, np);
         default: return launch_tiles<4, 1, 4, true, 3>(a, st, np);
         }
     }
@@ -753,10 +758,11 @@ hipError_t launch_kblock_f64_main(const KBlockArgs &a, hipStream_t st)
     switch (a.cfg >= 0 && a.cfg < kF64NumCfgs ? a.cfg : f64_config_id(A->m, A->n, a.sb)) {
     case 0: return launch_tiles<4, 2, 1, false, 4>(b, st);
     case 1: return launch_tiles<4, 2, 2, false, 3>(b, st);
-    case 3: return launch_tiles<4, 1, 8, false, 2>(b, st);
-    case 4: return launch_tiles<4, 1, 2, false, 4>(b, st);
+    case 3:
+    case 4: return launch_tiles<4, 1, 8, false, 2>(b, st);
     case 5: return launch_tiles<4, 2, 4, false, 2>(b, st);
-    case 6: return launch_tiles<4, 1, 1, false, 4>(b, st);
+    case 7: return launch_tiles<4, 1, 2, false, 4>(b, st);
+    case 8: return launch_tiles<4, 1, 1, false, 4>(b, st);
     default: return launch_tiles<4, 1, 4, false, 3>(b, st);
     }
 }

@@ -68,7 +68,7 @@ constexpr int64_t kGatherMinSB = 256;
 // ahead of them, which fills the chip: 128 x 64 tiles.  20000 x 512, s*b = 512, rows
 // of two blocks: 25 us for one block's launch, 11 us a block ahead (200000 x 1024,
 // bf16, one block's rows: 31 and 12).
-constexpr int32_t kGramCfg = 6, kGramBatchCfg = 0, kGramAheadCfg = 5;
+constexpr int32_t kGramCfg = 8, kGramBatchCfg = 5, kGramAheadCfg = 5;
 constexpr int64_t kGramAhead = 16;              // blocks of one such launch, at most
 constexpr size_t kGramAheadBytes = 64u << 20;   // and their memory
 // Largest rank of a low-rank factor (Nystrom landmarks, columns of Phi).

@@ -2,7 +2,7 @@
 // configuration chosen per (compute, n, sb) -- the FP64 product's, or the
 // single-problem bf16 / fp16 / bf16x3 product's -- filled by kdcd_autotune or
 // kdcd_tune_set, saved to and loaded from a plain text file ("compute n sb id"
-// per line).
+// per line; an id names the same tile in every version).
 #include <cstdio>
 #include <map>
 #include <mutex>
