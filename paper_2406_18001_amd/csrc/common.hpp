@@ -255,6 +255,7 @@ int64_t kblock_f64_row_groups(int cfg, int64_t m, int64_t n, int32_t sb, bool ba
 int f64_config_count();
 void f64_config_shape(int id, int *bm, int *bn, int *waves);
 int f64_config_id(int64_t m, int64_t n, int32_t sb);   // m < 0: any large m
+int f64_default_id(int64_t m, int32_t sb);             // without the tuning table
 int tune_lookup(int32_t compute, int64_t n, int32_t sb);   // -1: no entry
 void tune_store(int32_t compute, int64_t n, int32_t sb, int id);   // id < 0 removes
 // Panel memory of the CSR product: what every workspace holds, and what a

@@ -683,7 +683,7 @@ static int64_t tiles_of(int64_t m, int32_t sb, int tm, int tn)
 // as many as the block has (up to 64: the A stream is then read once per 64
 // sampled rows) on the 128-row tile, and smaller tiles, rows first, until there
 // are two workgroups per CU (m < 0: any large m).
-static int f64_default_id(int64_t m, int32_t sb)
+int f64_default_id(int64_t m, int32_t sb)
 {
     int tm = 2, tn = sb <= 16 ? 1 : (sb <= 32 ? 2 : 4);
     if (m >= 0 && tiles_of(m, sb, tm, tn) < 512) tm = 1;

@@ -1643,7 +1643,9 @@ kdcd_status run_graph_windowed(const SolveArgs &sa, const Layout &L)
 // Workgroups of the one-launch K-SVM solve (svm_persist.hip), or 0 when the solve
 // takes its ordinary launches: it needs memory of the call's own, writes nothing
 // but alpha and trace, and repeats the sums of a product on 64-row tiles with one
-// tile per row group, which is what small problems get.
+// tile per row group, which is what the built-in rule gives small problems.  (What the
+// tuning table says of n and s, from a matrix of any height, is not asked: it names the
+// tile of launches that this solve does not make.)
 int64_t persist_groups(const SolveArgs &sa)
 {
     const kdcd_options &o = sa.opt;
@@ -1654,7 +1656,7 @@ int64_t persist_groups(const SolveArgs &sa)
     if (groups == 0) return 0;
     for (const int64_t sb : {(int64_t)sa.s, sa.H % sa.s}) {
         if (sb == 0) continue;
-        const int id = f64_config_id(sa.A->m, sa.A->n, (int32_t)sb);
+        const int id = f64_default_id(sa.A->m, (int32_t)sb);
         int bm, bn, w;
         f64_config_shape(id, &bm, &bn, &w);
         if (bm != 64 || kblock_f64_row_groups(id, sa.A->m, sa.A->n, (int32_t)sb) != groups) return 0;
