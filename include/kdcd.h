@@ -566,6 +566,15 @@ kdcd_status kdcd_tune_load(const char *path);
  * workspaces that the library keeps for later calls (at most 1 GiB a device). */
 void kdcd_graph_cache_clear(void);
 
+/* For tests.  Small dense FP64 K-SVM solves run all outer iterations in one
+ * launch, whose workgroups wait for each other in polls; one that waits too
+ * long gives up, alpha is restored and the solve takes its ordinary launches.
+ * The polls before that for the calling thread's solves from now on (0: at
+ * once; < 0: the default), and how many of its solves so far ended in one
+ * launch or (gave_up != 0) gave up. */
+void kdcd_one_launch_polls(int32_t polls);
+int64_t kdcd_one_launch_count(int32_t gave_up);
+
 /* Device workspace a solve needs (problem: 0 = K-SVM, 1 = K-RR). */
 size_t kdcd_workspace_bytes(int32_t problem, const kdcd_matrix *A, const kdcd_kernel *kernel,
                             int32_t b, int32_t s, int32_t compute);

@@ -1664,6 +1664,17 @@ int64_t persist_groups(const SolveArgs &sa)
     return groups;
 }
 
+// Of the calling thread, for tests (kdcd_one_launch_*).
+struct PersistProbe {
+    int32_t polls = kPersistPolls;
+    int64_t ended = 0, gave_up = 0;
+};
+PersistProbe &persist_probe()
+{
+    static thread_local PersistProbe p;
+    return p;
+}
+
 // The one-launch solve in the workspace at `base`; *done says whether alpha is final
 // (otherwise it is as it was, and the ordinary launches take over).
 kdcd_status run_persist(const SolveArgs &sa, const Layout &L, char *base, size_t o_save, size_t o_slots,
@@ -1695,16 +1706,19 @@ kdcd_status run_persist(const SolveArgs &sa, const Layout &L, char *base, size_t
     pa.trace = sa.opt.trace;
     pa.slots = reinterpret_cast<uint64_t *>(base + o_slots);
     pa.status = status;
+    pa.polls = persist_probe().polls;
     if (launch_svm_persist(pa, groups, sa.st) != hipSuccess) {   // not all workgroups fit
         (void)hipGetLastError();
         return KDCD_OK;
     }
     const kdcd_status rc = read_status(status, sa.st);
     if ((int32_t)rc == kPersistGaveUp) {
+        ++persist_probe().gave_up;
         KDCD_HIP_TRY(hipMemcpyAsync(sa.alpha, base + o_save, sizeof(double) * (size_t)A->m,
                                     hipMemcpyDeviceToDevice, sa.st));
         return KDCD_OK;
     }
+    ++persist_probe().ended;
     *done = true;
     return rc;
 }
@@ -1840,6 +1854,13 @@ kdcd_options defaults(const kdcd_options *opt)
 }  // namespace
 
 extern "C" {
+
+void kdcd_one_launch_polls(int32_t polls) { persist_probe().polls = polls < 0 ? kPersistPolls : polls; }
+
+int64_t kdcd_one_launch_count(int32_t gave_up)
+{
+    return gave_up ? persist_probe().gave_up : persist_probe().ended;
+}
 
 void kdcd_graph_cache_clear(void)
 {

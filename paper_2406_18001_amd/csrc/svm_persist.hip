@@ -25,7 +25,7 @@
 //
 // Every wait ends: the launch is cooperative (all workgroups resident, or the
 // launch is refused and the solve takes its ordinary launches), and a poll gives
-// up after kMaxPolls rounds, which makes this workgroup (and so, in the same way, the
+// up after max_polls rounds (kPersistPolls; 0: at once), which makes this workgroup (and so, in the same way, the
 // others) return; the host then restores alpha and runs the ordinary launches.
 //
 // What bounds it: the exchange (store past the caches, poll, about 2 us) and the chain
@@ -53,7 +53,6 @@ constexpr int NT = 256;
 constexpr int BK = 16;
 constexpr int FIN_COLS = 8, FIN_PARTS = 32;      // the finish pass's reduction
 constexpr int kMaxWords = 4096;                  // G * s
-constexpr int kMaxPolls = 1 << 20;
 constexpr uint64_t kEmpty = 0x7ff4dead7ff4deadull;
 static_assert((uint32_t)kPersistEmptyWord == (uint32_t)kEmpty, "slots are filled by halves");
 
@@ -79,7 +78,7 @@ __global__ __launch_bounds__(NT) void svm_persist_kernel(
     const double *__restrict__ A, int64_t lda, int64_t m, int64_t n, const double *__restrict__ y,
     const double *__restrict__ norms, KParams kp, double nu, double omega, int32_t s, int64_t H,
     const int32_t *__restrict__ idx, double *alpha, double *__restrict__ trace, uint64_t *slots,
-    int32_t *status)
+    int32_t *status, int32_t max_polls)
 {
     constexpr int SBP = CB * 16;
     constexpr int PF = CB * NC / 4;              // 4-double segments of the sampled rows per thread
@@ -292,8 +291,8 @@ __global__ __launch_bounds__(NT) void svm_persist_kernel(
                 for (int u = 0; u < 8; ++u) v[u] = x0 + u * NT < words ? get(&slot[x0 + u * NT]) : 0;
 #pragma unroll
                 for (int u = 0; u < 8; ++u) open |= v[u] == kEmpty;
-            } while (open && ++polls < kMaxPolls);
-            if (open) dead = 1;
+            } while (open && ++polls < max_polls);
+            if (open || max_polls == 0) dead = 1;
 #pragma unroll
             for (int u = 0; u < 8; ++u)
                 if (x0 + u * NT < words) pv[x0 + u * NT] = __longlong_as_double((long long)v[u]);
@@ -379,8 +378,8 @@ __global__ __launch_bounds__(NT) void svm_persist_kernel(
     bool late = false;
     for (int q = lane; q < G; q += 64) {
         int polls = 0;
-        while (get(&slots[(n_outer % 3) * (int64_t)G * s + q]) == kEmpty && ++polls < kMaxPolls) {}
-        late |= polls == kMaxPolls;
+        while (get(&slots[(n_outer % 3) * (int64_t)G * s + q]) == kEmpty && ++polls < max_polls) {}
+        late |= polls >= max_polls;
     }
     if (__ballot(late) != 0) {
         if (lane == 0) set_status(status, kPersistGaveUp);
@@ -439,7 +438,8 @@ hipError_t launch_svm_persist(const SvmPersistArgs &a, int64_t groups, hipStream
     double *alpha = a.alpha, *trace = a.trace;
     uint64_t *slots = a.slots;
     int32_t *status = a.status;
-    void *args[] = {&Av, &lda, &m, &n, &y, &norms, &kp, &nu, &omega, &s, &H, &idx, &alpha, &trace, &slots, &status};
+    int32_t polls = a.polls;
+    void *args[] = {&Av, &lda, &m, &n, &y, &norms, &kp, &nu, &omega, &s, &H, &idx, &alpha, &trace, &slots, &status, &polls};
     return hipLaunchCooperativeKernel(f, dim3((unsigned)groups), dim3(NT), args, 0, st);
 }
 

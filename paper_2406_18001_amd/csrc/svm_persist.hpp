@@ -7,6 +7,7 @@ namespace kdcd {
 
 constexpr int32_t kPersistEmptyWord = 0x7ff4dead;   // both halves of an empty exchange word
 constexpr int32_t kPersistGaveUp = -1000;           // status: a wait ran out, alpha must be restored
+constexpr int32_t kPersistPolls = 1 << 20;          // a second and more
 // Shorter solves keep their ordinary launches: an outer iteration saves 6 us or more, the
 // start costs 50 us more.
 constexpr int64_t kPersistMinOuter = 16;
@@ -22,6 +23,7 @@ struct SvmPersistArgs {
     double *alpha, *trace;   // trace: H updates or null
     uint64_t *slots;         // 3 * groups * s words, every half kPersistEmptyWord
     int32_t *status;
+    int32_t polls;           // rounds of a wait before the launch gives up
 };
 // Workgroups of the launch, or 0 when the problem is not one for it (also when they
 // would not all be resident).
