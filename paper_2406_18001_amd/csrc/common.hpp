@@ -194,6 +194,8 @@ struct KBlockArgs {
     // -1; a chunk of sampled rows that cannot exceed the panel then skips the
     // broadcast launch that would only run for an overflowing chunk
     int64_t csr_max_row = -1;
+    // CSR: no row is longer than twice the average (false: some is, or not known)
+    bool csr_even = false;
     bool csr_built = false;  // the first chunk's dense-head panel was built ahead
     // dense single-problem FP64 product: tile configuration, resolved once by
     // the caller together with the row-group count the finish pass sums

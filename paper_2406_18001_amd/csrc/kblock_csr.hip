@@ -909,7 +909,7 @@ bool csr_takes_panel(const KBlockArgs &a)
     // (rows of about average length fill nine tenths of a dense-head chunk)
     const bool head = sb > 16 && avg * std::min(sb, HD_NJ) <= 0.9 * HD_CAP;
     if (head && p.lpr < HD_NJ) return false;
-    if (a.csr_max_row < 0 || (double)a.csr_max_row > 2.0 * avg) return true;    // uneven, or not known
+    if (!a.csr_even) return true;
     if (head) return sb > HD_NJ;
     if (sb <= 8 && avg < kCsrWaveMinAvg) return false;
     return !(sb <= 4 && avg * sb <= CSR_VMAX && A->n > kCodeInCache);

@@ -560,7 +560,26 @@ struct SolveArgs {
     kdcd_options opt;
     hipStream_t st;
     int64_t csr_max_row = -1;   // CSR: longest row of A, when measured (-1: unknown)
+    bool csr_even = false;      // CSR: it is at most twice the average row
 };
+
+// Longest row of a CSR matrix (one reduction and a wait; -1: of a malformed one), with
+// 8 bytes of device memory at scratch.
+kdcd_status csr_longest_row(const kdcd_matrix *A, char *scratch, hipStream_t st, int64_t *longest)
+{
+    unsigned long long *dmax = reinterpret_cast<unsigned long long *>(scratch);
+    unsigned long long hmax = ~0ull;
+    KDCD_HIP_TRY(launch_csr_row_max(A, dmax, st));
+    KDCD_HIP_TRY(hipMemcpyAsync(&hmax, dmax, sizeof(hmax), hipMemcpyDeviceToHost, st));
+    KDCD_HIP_TRY(hipStreamSynchronize(st));
+    *longest = hmax <= (unsigned long long)A->n ? (int64_t)hmax : -1;
+    return KDCD_OK;
+}
+
+bool csr_rows_even(const kdcd_matrix *A, int64_t longest)
+{
+    return longest >= 0 && (double)longest * (double)A->m <= 2.0 * (double)A->nnz;
+}
 
 // Whether prepare_lowp's copy makes the FP64 norms as well (no pass of their own).
 bool lowp_makes_norms(const kdcd_matrix *A, int32_t compute)
@@ -1168,6 +1187,7 @@ kdcd_status enqueue_solve(const SolveArgs &sa, const Layout &L, char *wsbase, St
         base.csr_panel = ws.at<void>(L.panel);
         base.csr_panel_bytes = L.panel_bytes;
         base.csr_max_row = sa.csr_max_row;
+        base.csr_even = sa.csr_even;
         base.csr_sb = sa.s * sa.b;
         if (R.setup) KDCD_HIP_TRY(launch_csr_panel_init(base, st));
     }
@@ -1395,6 +1415,7 @@ struct GraphEntry {
     hipGraphExec_t exec = nullptr;
     char *ws = nullptr;
     bool owned = false;
+    bool csr_even = false;   // as found when the graph was captured: it chose the kernels
     uint64_t used = 0;
 };
 
@@ -1439,12 +1460,12 @@ struct KeyBuilder {
 
 // The cache entry of `key` on the current device, captured and instantiated
 // on first use (with c.mu held; the same call in a workspace of another size is another
-// entry): prepare(base) is synchronous set-up before
+// entry): prepare(entry) is synchronous set-up before
 // the capture (host-to-device copies of data the graph reads); enqueue(base,
 // stream) is the work to capture.
 GraphEntry *graph_entry(GraphCache &c, const std::string &key, size_t bytes,
                         const kdcd_options &opt,
-                        const std::function<kdcd_status(char *)> &prepare,
+                        const std::function<kdcd_status(GraphEntry &)> &prepare,
                         const std::function<kdcd_status(char *, hipStream_t)> &enqueue,
                         kdcd_status &rc)
 {
@@ -1482,7 +1503,7 @@ GraphEntry *graph_entry(GraphCache &c, const std::string &key, size_t bytes,
         ne.ws = static_cast<char *>(p);
         ne.owned = true;
     }
-    rc = prepare ? prepare(ne.ws) : KDCD_OK;
+    rc = prepare ? prepare(ne) : KDCD_OK;
     hipGraph_t g = nullptr;
     if (rc == KDCD_OK) {
         if (hipStreamBeginCapture(c.capture[dev], hipStreamCaptureModeThreadLocal) != hipSuccess) {
@@ -1515,7 +1536,7 @@ GraphEntry *graph_entry(GraphCache &c, const std::string &key, size_t bytes,
 // A whole call captured as one graph and replayed by calls with identical
 // arguments.
 kdcd_status run_graph(const std::string &key, size_t bytes, const kdcd_options &opt,
-                      hipStream_t st, const std::function<kdcd_status(char *)> &prepare,
+                      hipStream_t st, const std::function<kdcd_status(GraphEntry &)> &prepare,
                       const std::function<kdcd_status(char *, hipStream_t)> &enqueue)
 {
     GraphCache &c = graph_cache();
@@ -1583,7 +1604,18 @@ kdcd_status check_monitor(const kdcd_matrix *A, const kdcd_options &o)
 // whole call is then captured instead).
 constexpr int32_t kGraphWindow = 16;
 
-kdcd_status run_graph_windowed(const SolveArgs &sa, const Layout &L)
+// Before a solve's graph is captured: what its choice of CSR kernels needs (a property
+// of the rows' lengths then, which decides speed only).
+kdcd_status csr_graph_setup(SolveArgs &sa, const Layout &L, GraphEntry &e)
+{
+    if (sa.A->format != KDCD_CSR) return KDCD_OK;
+    int64_t longest = -1;
+    const kdcd_status rc = csr_longest_row(sa.A, e.ws + L.status + 8, sa.st, &longest);
+    sa.csr_even = e.csr_even = csr_rows_even(sa.A, longest);
+    return rc;
+}
+
+kdcd_status run_graph_windowed(SolveArgs sa, const Layout &L)
 {
     const int64_t sbw = (int64_t)sa.s * sa.b;
     const int64_t n_full = sa.H / sa.s;
@@ -1607,7 +1639,7 @@ kdcd_status run_graph_windowed(const SolveArgs &sa, const Layout &L)
     std::lock_guard<std::mutex> lk(c.mu);
     kdcd_status rc = KDCD_OK;
     GraphEntry *e = graph_entry(
-        c, kb.k, bytes, sa.opt, nullptr,
+        c, kb.k, bytes, sa.opt, [&](GraphEntry &e) { return csr_graph_setup(sa, L, e); },
         [&](char *base, hipStream_t cs) {
             int64_t *cnt = reinterpret_cast<int64_t *>(base + o_cnt);
             int32_t *win = reinterpret_cast<int32_t *>(base + o_win);
@@ -1624,6 +1656,7 @@ kdcd_status run_graph_windowed(const SolveArgs &sa, const Layout &L)
         },
         rc);
     if (!e) return rc;
+    sa.csr_even = e->csr_even;
     StageTimer off;
     SolveRange head;                       // set-up and the first outer iteration
     head.k_end = 1;
@@ -1744,7 +1777,7 @@ Layout solve_layout(const SolveArgs &sa, bool full)
     return L;
 }
 
-kdcd_status run_solve_graph(const SolveArgs &sa, const Layout &L)
+kdcd_status run_solve_graph(SolveArgs sa, const Layout &L)
 {
     const kdcd_status rc = run_graph_windowed(sa, L);
     if (rc != KDCD_ERR_UNSUPPORTED) return rc;
@@ -1757,7 +1790,8 @@ kdcd_status run_solve_graph(const SolveArgs &sa, const Layout &L)
     kb.add(sa.C); kb.add(sa.lambda); kb.add(sa.b); kb.add(sa.s); kb.add(sa.H);
     kb.add(sa.idx); kb.add(sa.alpha);
     kb.options(sa.opt);
-    return run_graph(kb.k, L.total, sa.opt, sa.st, nullptr,
+    return run_graph(kb.k, L.total, sa.opt, sa.st,
+                     [&](GraphEntry &e) { return csr_graph_setup(sa, L, e); },
                      [&](char *base, hipStream_t cs) {
                          SolveArgs g = sa;
                          g.st = cs;
@@ -1797,15 +1831,10 @@ kdcd_status run_solve(const SolveArgs &sa)
     }
     SolveArgs sx = sa;
     if (sa.A->format == KDCD_CSR && sa.A->m > 0) {
-        // the longest row (one reduction and a wait at the start of the call),
-        // so that chunks which cannot overflow the dense-head panel skip the
+        // the longest row: chunks which cannot overflow the dense-head panel skip the
         // gated broadcast launch (kept by graph calls, which cannot wait)
-        unsigned long long *dmax = reinterpret_cast<unsigned long long *>(ws.at<char>(L.status) + 8);
-        unsigned long long hmax = ~0ull;
-        KDCD_HIP_TRY(launch_csr_row_max(sa.A, dmax, sa.st));
-        KDCD_HIP_TRY(hipMemcpyAsync(&hmax, dmax, sizeof(hmax), hipMemcpyDeviceToHost, sa.st));
-        KDCD_HIP_TRY(hipStreamSynchronize(sa.st));
-        if (hmax <= (unsigned long long)sa.A->n) sx.csr_max_row = (int64_t)hmax;
+        if ((rc = csr_longest_row(sa.A, ws.at<char>(L.status) + 8, sa.st, &sx.csr_max_row)) != KDCD_OK) return rc;
+        sx.csr_even = csr_rows_even(sa.A, sx.csr_max_row);
     }
     StageTimer timer;
     timer.on = sa.opt.profile != nullptr;

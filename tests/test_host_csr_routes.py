@@ -52,3 +52,25 @@ print(launched())
     assert r.stdout.count(kernel) >= 3
     # the panel memory is laid out for the kernel that reads it
     assert ("pp_init_kernel" in r.stdout) == (kernel == PANEL)
+
+
+@pytest.mark.parametrize("longest,kernel,other", [(170, BROADCAST, PANEL), (900, PANEL, BROADCAST)])
+@pytest.mark.parametrize("H", [5, 40])                # one graph of the whole call, a graph of a window
+def test_kernel_of_a_graph(stub, longest, kernel, other, H):
+    """The rows' lengths are looked at when the graph is captured; what runs around its
+    replays is of the same kind, also when they have changed since."""
+    body = f"""
+from tests.hip_host import *
+a = (f64 * 60000)()
+A = csr(60000, 1000000, 60000 * 113)
+for longest in ({longest}, 170, 900):
+    put("row_max", longest, ctypes.c_uint64)
+    assert solve(A, 1, 1, {H}, "svm", flags=GRAPH, alpha=a) == 0
+print(launched())
+"""
+    r = subprocess.run([sys.executable, "-c", body, stub], capture_output=True, text=True, timeout=120, cwd=os.path.dirname(HERE))
+    assert r.returncode == 0, r.stdout + r.stderr
+    # (a panel chunk that may overflow has a gated kernel of the other kind after it)
+    assert kernel in r.stdout and (kernel == PANEL or other not in r.stdout)
+    assert ("pp_init_kernel" in r.stdout) == (kernel == PANEL)
+    assert r.stdout.count("csr_row_max_kernel") == 1
