@@ -86,7 +86,7 @@ struct HeadBuildLds {
     int32_t hcode[HD_HS];       // first entry of the column, then its code
     int64_t rowbeg[HD_NJ];
     int32_t rowoff[HD_NJ + 1];
-    int32_t wsum[2][HD_EPT][HD_BUILD_NT / 64];
+    __align__(16) int32_t wsum[2][HD_EPT][HD_BUILD_NT / 64];   // (read 16 bytes at a time)
     int32_t hist[HD_NJ + 2];
     int32_t info[1];
 };
