@@ -90,7 +90,10 @@ typedef struct {
 } kdcd_matrix;
 
 /* Optional per-call stage timings, measured with HIP events recorded on the
- * call's stream around every launch of the named stage. */
+ * call's stream around every launch of the named stage.  A profiled solve has a
+ * launch for each: it is not run in one launch (small dense K-SVM), and r is
+ * summed by the finish stage also where a plain K-SVM solve leaves that to the
+ * recurrence. */
 typedef struct {
     double kblock_ms;        /* kernel-block product + map + r partials + Gram    */
                              /* (the product kernel alone where the Gram rows are */
@@ -115,7 +118,9 @@ typedef struct {
  * current contents of A, y, idx and alpha.  A cache entry keeps its own
  * workspace (allocated once with hipMalloc) unless opt->workspace is given,
  * which then must stay valid while the entry lives.  Graph-mode calls are
- * serialised by one lock.  With a profile, only total_ms is reported.
+ * serialised by one lock.  With a profile, only total_ms is reported.  (Small
+ * dense FP64 K-SVM solves run in one launch without the flag and are faster
+ * then.)
  * kdcd_ksvm_solve / kdcd_krr_solve without trace, snapshots, profile or a
  * caller workspace, with at least 18 whole blocks (floor(H/s) >= 18), are
  * replayed by windows instead: one graph holds 16 outer iterations -- a
@@ -142,7 +147,7 @@ typedef struct {
 /*
  * Lookahead loop (kdcd_krr_solve and kdcd_krr_solve_noalloc; dense A, any
  * compute, b <= 8, 256 <= s*b <= 512, at least two outer iterations, no
- * snapshots; FP64 also needs n a multiple of 16 with 16-byte aligned rows;
+ * snapshots; FP64 only with n a multiple of 16 and 16-byte aligned rows;
  * the monitor only in FP64 and without a caller workspace, whose size does
  * not include the second stored kernel block the loop then keeps): the s-step
  * recurrence of index
@@ -154,7 +159,8 @@ typedef struct {
  * times the updates to r_{k+1} and the updates to alpha, which is Algorithm
  * 4's r_{k+1} = U_{k+1}^T alpha up to rounding.  Used by default
  * where a rule on m, n, s, b and the compute type expects it to be the faster;
- * KDCD_FLAG_LOOKAHEAD asks for it at any size, KDCD_FLAG_SERIAL never.  Calls
+ * KDCD_FLAG_LOOKAHEAD takes it wherever these limits allow, KDCD_FLAG_SERIAL
+ * never.  Calls
  * that KDCD_FLAG_GRAPH replays by windows run the serial loop.
  */
 /* Any other bit of flags is refused with KDCD_ERR_INVALID_ARG. */
@@ -173,7 +179,7 @@ typedef struct {
     int32_t flags;           /* KDCD_FLAG_*                                                  */
     double *snapshots;       /* device, (ceil(ceil(H/s)/snapshot_every)) x m, row-major       */
     double *trace;           /* device, H*b: theta (K-SVM) / Delta alpha (K-RR) per update    */
-    void *workspace;         /* device; NULL = allocated on `stream` and freed before return  */
+    void *workspace;         /* device; NULL = the library's own (kdcd_graph_cache_clear)    */
     size_t workspace_bytes;
     kdcd_profile *profile;   /* host; NULL = no timing                                      */
     int32_t monitor_every;   /* > 0: convergence monitor every this many outer iterations   */
@@ -524,7 +530,7 @@ kdcd_status kdcd_ksvm_solve_sampled(const kdcd_matrix *A, const double *y,
  * (compute, n, sb) from a process-wide table, else by a built-in rule.
  * Entries come from kdcd_autotune (which times every configuration on the
  * caller's matrix) or kdcd_tune_set, and can be saved to and loaded from a
- * text file.  A launch reads the table once and its finish pass uses the same
+ * text file (an id names the same tile in every version).  A launch reads the table once and its finish pass uses the same
  * configuration, so the table may change while solves run (they then take
  * the old or the new entry).
  * ------------------------------------------------------------------------- */
@@ -537,7 +543,9 @@ kdcd_status kdcd_ksvm_solve_sampled(const kdcd_matrix *A, const double *y,
 int32_t kdcd_tune_configs(int32_t compute, int32_t *bm, int32_t *bn, int32_t *waves, int32_t max);
 /* Pin configuration `id` for (compute, n, sb); id < 0 removes the entry. */
 kdcd_status kdcd_tune_set(int32_t compute, int64_t n, int32_t sb, int32_t id);
-/* The configuration a launch with (compute, n, sb) uses now (-1: invalid). */
+/* The configuration of a launch with (compute, n, sb) on many rows: the table's
+ * entry, which is used whatever the number of rows, or else the built-in rule's
+ * (which takes smaller FP64 tiles for few rows) (-1: invalid). */
 int32_t kdcd_tune_get(int32_t compute, int64_t n, int32_t sb);
 /* Time every configuration on A with sb sampled rows (evenly strided),
  * three rounds of `reps` launches each (a configuration counts with its
@@ -562,8 +570,11 @@ kdcd_status kdcd_tune_save(const char *path);
 kdcd_status kdcd_tune_load(const char *path);
 
 /* Destroy every graph cached by KDCD_FLAG_GRAPH calls and free the
- * workspaces they own (no call may be running), and return the freed
- * workspaces that the library keeps for later calls (at most 1 GiB a device). */
+ * workspaces they own (no call may be running), and return the workspaces that
+ * the library keeps: one that a call allocated (opt->workspace NULL) stays with
+ * it for later calls, at most 16 and 1 GiB of them a device, which other
+ * allocators of the process can have only after this.  (An allocation of the
+ * library's own that fails takes them back by itself.) */
 void kdcd_graph_cache_clear(void);
 
 /* For tests.  Small dense FP64 K-SVM solves run all outer iterations in one

@@ -18,8 +18,8 @@
 //
 // What bounds it: the panel reads, LPR * 8 bytes per hit through L1 / L2 (news20
 // recipe, 64 sampled rows: 5.5e6 hits * 512 B = 2.8 GB against 110 MB of CSR
-// arrays).  Measured there, per pass over 64 sampled rows: product 265 us (3.9 GB
-// of L2 requests at 14.7 TB/s, 0.8 GB past L2), claim 16, scatter 5.5; the chunked
+// arrays).  Measured there, per pass over 64 sampled rows: product 267 us (3.9 GB
+// of L2 requests at 14.5 TB/s, 0.8 GB past L2), claim 14, scatter 8; the chunked
 // LDS hash it replaces took 2310 us (one pass over A per 3072 stored entries of the
 // sampled rows, a table build in every workgroup each time), and with 1 / 8 / 32
 // sampled rows 124 / 457 / 1124 us per outer iteration against 117 / 144 / 206.

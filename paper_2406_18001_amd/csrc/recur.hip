@@ -229,7 +229,7 @@ __global__ __launch_bounds__(NT) void ksvm_recur_kernel(const KsvmRecurDesc D, c
 // The recurrence of an index block of a CSR problem (sb <= 64) and, in a second
 // workgroup, the dense-head panel of the next block's first chunk, which needs only
 // its indices: 12 us a block no longer in the way (100000 rows of 50, s = 32: 9.2 for
-// the recurrence and 11.9 for the panel; both in 12.5).
+// the recurrence and 11.9 for the panel; both in 11.9).
 constexpr int RB_NT = 512;                     // threads of the recurrence
 __global__ __launch_bounds__(HD_BUILD_NT) void ksvm_recur_build_kernel(const KsvmRecurDesc D,
                                                                        const int32_t *__restrict__ S, int32_t sb,

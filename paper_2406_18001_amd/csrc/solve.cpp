@@ -748,9 +748,10 @@ bool lookahead_pays(int64_t m, int64_t n, int32_t b, int32_t s, int32_t compute)
 }
 
 // Whether a K-RR solve runs the lookahead loop (see LookaheadArgs): dense FP64
-// with a gathered Gram, b <= 8, 256 <= s*b <= 512, whole product tiles along
-// K, no snapshots (the monitor only with the second stored kernel block), the
-// whole solve in one call.
+// with a gathered Gram, b <= 8, 256 <= s*b <= 512, no snapshots (the monitor only with
+// the second stored kernel block), the whole solve in one call.  FP64: whole chunks
+// along K and 16-byte rows, which the product itself does not need; the loop is
+// measured and tested on such matrices only.
 bool lookahead_use(const SolveArgs &sa, const Layout &L, const KBlockArgs &kb,
                    const SolveRange &R)
 {

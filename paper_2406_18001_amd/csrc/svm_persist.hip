@@ -1,7 +1,7 @@
 // K-SVM on small dense problems: all outer iterations in one launch.
 //
-// A small outer iteration (2000 x 64, s = 1: 1 MB of A, 0.3 MFLOP) is three
-// kernels that wait for each other: 17.6 us, nearly all of it launches, first
+// A small outer iteration (2000 x 64, s = 1: 1 MB of A, 0.3 MFLOP) is two or three
+// kernels that wait for each other: 12.9 us, nearly all of it launches, first
 // loads and drained pipelines.  Here one cooperative launch keeps G = ceil(m/64)
 // workgroups on the chip for the whole solve.  Workgroup g holds rows 64 g ..
 // 64 g + 63 of A in registers and their beta = alpha y in LDS; per outer iteration
@@ -31,9 +31,9 @@
 // What bounds it: the exchange (store past the caches, poll, about 2 us) and the chain
 // behind it -- 16 dependent MFMAs per 64 columns, the map, three workgroup barriers, the
 // recurrence.  Measured per outer iteration, ordinary launches against this: 2000 x 64,
-// s = 1 / 8 / 16: 14.7 / 14.8 / 16.2 -> 5.2 / 6.5 / 8.3 us; 2000 x 256, s = 1: 17.8 -> 9.7;
-// 20000 x 64, s = 8: 16.5 -> 9.6.  The cooperative launch and the exchange memory cost
-// 50 us more per solve.  With 64 sampled rows the recurrence of one wave (LDS reads in
+// s = 1 / 8 / 16: 12.9 / 13.4 / 14.0 -> 5.0 / 6.6 / 8.3 us; 2000 x 256, s = 1: 15.7 -> 9.6;
+// 20000 x 64, s = 8: 15.1 -> 9.6.  The cooperative launch and the exchange memory cost
+// 20 us more per solve.  With 64 sampled rows the recurrence of one wave (LDS reads in
 // its chain) takes what the launches did, so s <= 32.
 //
 // All sums are formed in the order of the ordinary launches (the 64-row tiles of

@@ -8,8 +8,8 @@ namespace kdcd {
 constexpr int32_t kPersistEmptyWord = 0x7ff4dead;   // both halves of an empty exchange word
 constexpr int32_t kPersistGaveUp = -1000;           // status: a wait ran out, alpha must be restored
 constexpr int32_t kPersistPolls = 1 << 20;          // a second and more
-// Shorter solves keep their ordinary launches: an outer iteration saves 6 us or more, the
-// start costs 50 us more.
+// Shorter solves keep their ordinary launches: an outer iteration saves 5.5 us or more, the
+// start costs 20 us more.
 constexpr int64_t kPersistMinOuter = 16;
 
 struct SvmPersistArgs {
